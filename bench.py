@@ -48,9 +48,9 @@ METRIC = "EDT Mvoxels/s + % HBM roofline; p50/p99 insert→EDT→query cycle lat
 XY_BYTES_PER_VOXEL = 1 + 4      # occupancy byte in, packed 2D site out
 Z_BYTES_PER_VOXEL = 4 + 8       # packed 2D site in, d2 + site out
 EDT_BYTES_PER_VOXEL = 9         # compulsory: occupancy in, d2 + site out
-# the kernels of each pass on the control-cycle map (the lean 64-column tiles)
-XY_KERNELS = ["k_row_records", "k_edt_xy_lean"]
-Z_KERNELS = ["k_edt_z_lean"]
+# the kernels of each pass on the control-cycle map (the search tiles)
+XY_KERNELS = ["k_row_records", "k_edt_xy_search"]
+Z_KERNELS = ["k_edt_z_search"]
 
 
 # HBM traffic of the EDT kernels from hardware counters: a committed summary
@@ -59,7 +59,7 @@ Z_KERNELS = ["k_edt_z_lean"]
 # only while the kernel sources hash to what they were when it was taken.
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "edt_cycle256_pmc_traffic.md")
 EDT_KERNEL_SOURCES = ("paper_2407_02363_amd/csrc/common.h", "paper_2407_02363_amd/csrc/edt_tiles.h",
-                      "paper_2407_02363_amd/csrc/edt_lean.h", "paper_2407_02363_amd/csrc/edt_core.hip")
+                      "paper_2407_02363_amd/csrc/edt_search.h", "paper_2407_02363_amd/csrc/edt_core.hip")
 
 
 def edt_source_hash():

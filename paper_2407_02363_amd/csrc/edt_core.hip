@@ -1,11 +1,10 @@
 // The exact squared EDT on gfx950 for one map: the xy-tile kernel (steps 1-3
 // of Sec. III-C in every slice) and the z-tile kernel (step 4), their
-// launchers and the tile heuristics.  The tile code is in edt_tiles.h (every
-// shape and tiling) and edt_lean.h (the 64-column tiles of maps up to 256 rows
-// and 128 slices).
+// launchers and the tile heuristics.  The tile code is in edt_search.h (maps
+// with every axis up to 512) and edt_tiles.h (every shape and tiling).
 #include <algorithm>
 
-#include "edt_lean.h"
+#include "edt_search.h"
 
 namespace edtmi {
 
@@ -43,7 +42,8 @@ __global__ __launch_bounds__(NTX) void k_edt_xy(EdtMapSet s)
 
 // Row records (step 1) of every map of the set: each wave takes
 // record_rows_per_wave(nx) whole rows of one map, four waves per work-group;
-// s.m[i].begin is the map's first wave.
+// s.m[i].begin is the map's first wave.  SEARCH: in the search tiles' format.
+template <bool SEARCH>
 __global__ __launch_bounds__(256) void k_row_records(EdtMapSet s)
 {
     const int wv = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
@@ -53,10 +53,12 @@ __global__ __launch_bounds__(256) void k_row_records(EdtMapSet s)
     const int per = record_rows_per_wave(d.occ, d.nx);
     const int row0 = (wv - d.begin) * per;
     const int nrows = min(per, d.ny * d.nz - row0);
-    if (record_words(d.occ, d.nx))
-        row_summary_words(d.occ, d.nx, (size_t)row0, nrows, row_records(d.d2, d.nx, d.ny, d.nz));
-    else
-        row_summary(d.occ, d.nx, (size_t)row0, nrows, row_records(d.d2, d.nx, d.ny, d.nz));
+    auto run = [&](const auto& rec) {
+        if (record_words(d.occ, d.nx)) row_summary_words(d.occ, d.nx, (size_t)row0, nrows, rec);
+        else row_summary(d.occ, d.nx, (size_t)row0, nrows, rec);
+    };
+    if constexpr (SEARCH) run(search::records_of(d.d2));
+    else run(row_records(d.d2, d.nx, d.ny, d.nz));
 }
 
 // Steps 2-3 from the row records.
@@ -85,27 +87,32 @@ __global__ __launch_bounds__(NTZ) void k_edt_z(EdtMapSet s)
     edt_z_tile<TW, WIDE, NTZ>(d.d2, d.site, d.nx, d.ny, d.nz, d.ntx, T - d.begin, lds);
 }
 
-// Lean tiles (edt_lean.h): 64 columns, one wave per band.
-__global__ __launch_bounds__(256) void k_edt_z_lean(EdtMapSet s)
+// Search tiles (edt_search.h).  A launch for one map takes the map itself as
+// its argument (Set = EdtMap): one scalar load brings all of it, where a set
+// costs a chain of dependent ones (the count, the begins, the gate, the map).
+__device__ __forceinline__ const EdtMap& tile_map(const EdtMap& m, int) { return m; }
+__device__ __forceinline__ const EdtMap& tile_map(const EdtMapSet& s, int T) { return s.m[map_of(s, T)]; }
+
+template <int NMAX, int C, int BAND, class Set>
+__global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_z_search(Set s, int waves)
 {
+    extern __shared__ uint32_t lds[];
     const int T = (int)blockIdx.x;
-    const EdtMap& d = s.m[map_of(s, T)];
+    const EdtMap& d = tile_map(s, T);
     if (gated_off(d)) return;
-    __shared__ lean::ZLds lds;
-    lean::z_tile(d.d2, d.site, d.nx, d.ny, d.nz, d.ntx, T - d.begin, (int)threadIdx.x, lds);
+    search::z_tile<NMAX, C, BAND>(d.d2, d.site, d.nx, d.ny, d.nz, T - d.begin, BAND * waves, lds);
 }
 
-// Ent = uint16_t (narrow stack entries) when every map has at most 256 columns.
-template <typename Ent>
-__global__ __launch_bounds__(512) void k_edt_xy_lean(EdtMapSet s)
+template <int NMAX, int C, int BAND, class Set>
+__global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_xy_search(Set s, int waves)
 {
+    extern __shared__ uint32_t lds[];
     // as in k_edt_xy: chunks of 16 tiles per XCD, rotating over the XCDs
-    const int T = xcd_chunk_remap(blockIdx.x, s.total, 16);
-    const EdtMap& d = s.m[map_of(s, T)];
+    const int T = xcd_chunk_remap(blockIdx.x, gridDim.x, 16);
+    const EdtMap& d = tile_map(s, T);
     if (gated_off(d)) return;
-    __shared__ lean::XyLdsT<Ent> lds;
-    lean::xy_tile<Ent>(row_records(d.d2, d.nx, d.ny, d.nz), reinterpret_cast<uint32_t*>(d.site), d.nx, d.ny,
-                       d.ntx, T - d.begin, lds);
+    search::xy_tile<NMAX, C, BAND>(search::records_of(d.d2).r, reinterpret_cast<uint32_t*>(d.site), d.nx, d.ny,
+                                   d.ntx, T - d.begin, BAND * waves, lds);
 }
 
 // Allow dynamic LDS beyond the 64 KiB default (gfx950 has 160 KiB per
@@ -135,21 +142,18 @@ bool rows_first(const EdtMapSet& s)
     return true;
 }
 
-// The lean tiles take maps with every axis <= 512 (24-bit arithmetic), up to
-// 256 rows (xy) or 128 slices (z), and rows of 64 voxels or more (the row
-// records must fit into d2).
-bool lean_xy_ok(const EdtMapSet& s)
+// The search tiles take maps with every axis <= 512; the xy ones keep their
+// row records in d2.
+bool search_xy_ok(const EdtMapSet& s)
 {
     if (s.wide) return false;
     for (int i = 0; i < s.n; ++i)
-        if (s.m[i].ny > lean::XY_MAX || s.m[i].nx < 64 || !s.m[i].d2) return false;
+        if (!search::records_fit(s.m[i].nx) || !s.m[i].d2) return false;
     return true;
 }
 
-bool lean_z_ok(const EdtMapSet& s) { return !s.wide && s.nz_max <= lean::Z_MAX; }
-
 // Step 1 of every map of the set once per row, into the maps' d2 buffers.
-int launch_row_records(const EdtMapSet& s, hipStream_t st)
+int launch_row_records(const EdtMapSet& s, bool search, hipStream_t st)
 {
     static thread_local EdtMapSet r;   // the maps counted in waves (2.3 KiB: off the stack)
     r = s;
@@ -160,39 +164,72 @@ int launch_row_records(const EdtMapSet& s, hipStream_t st)
         waves += (s.m[i].ny * s.m[i].nz + per - 1) / per;
     }
     r.total = waves;
-    hipLaunchKernelGGL(k_row_records, dim3((waves + 3) / 4), dim3(256), 0, st, r);
+    if (search) hipLaunchKernelGGL(k_row_records<true>, dim3((waves + 3) / 4), dim3(256), 0, st, r);
+    else hipLaunchKernelGGL(k_row_records<false>, dim3((waves + 3) / 4), dim3(256), 0, st, r);
     return check_launch("k_row_records");
+}
+
+// One pass of the search tiles; n = the longest line of the pass.
+template <int NMAX, int BAND>
+int launch_search_t(const EdtMapSet& s, bool z_pass, int n, hipStream_t st)
+{
+    // chunks of 4 sites; of 8 beyond 256 positions, where the chunk minima of
+    // a z work-group would not fit into the local memory beside its sites, and
+    // testing twice the chunks costs the xy pass more than it saves
+    // (512 x 512 x 128 frame 84 against 93 us, 512^3 blobs 431 against 436)
+    constexpr int C = NMAX <= 256 ? 4 : 8;
+    const int nw = (n + BAND - 1) / BAND, np = nw * BAND;
+    auto go = [&](auto kernel, bool& done, size_t lds, const auto& arg, const char* name) -> int {
+        int rc = allow_lds(kernel, done);
+        if (rc) return rc;
+        hipLaunchKernelGGL(kernel, dim3(s.total), dim3(64 * nw), lds, st, arg, nw);
+        return check_launch(name);
+    };
+    static bool done[4];
+    if (z_pass) {
+        const size_t lds = (size_t)(np + np / C) * 256;
+        return s.n == 1 ? go(k_edt_z_search<NMAX, C, BAND, EdtMap>, done[0], lds, s.m[0], "k_edt_z_search")
+                        : go(k_edt_z_search<NMAX, C, BAND, EdtMapSet>, done[1], lds, s, "k_edt_z_search");
+    }
+    const size_t lds = (size_t)(np + np / C) * 128;
+    return s.n == 1 ? go(k_edt_xy_search<NMAX, C, BAND, EdtMap>, done[2], lds, s.m[0], "k_edt_xy_search")
+                    : go(k_edt_xy_search<NMAX, C, BAND, EdtMapSet>, done[3], lds, s, "k_edt_xy_search");
+}
+
+int launch_search(const EdtMapSet& s, bool z_pass, hipStream_t st)
+{
+    const int n = z_pass ? s.nz_max : s.ny_max;
+    // Bands of 32 rows or 16 slices keep 8 waves per SIMD resident with the
+    // local memory of a work-group of 128 or 256 positions (z bands of 32 only
+    // 4: 512 x 512 x 128 frame 87 against 76 us).  Launches with fewer waves
+    // than that take shorter bands: 64^3 boxes 34 us with bands of 32, 17 with
+    // 8; the xy pass of one 256 x 256 x 128 frame 40 us with 32, 36 with 16.
+    auto waves = [&](int band) { return (int64_t)s.total * ((n + band - 1) / band); };
+    int band = z_pass ? 16 : 32;
+    while (band > 8 && waves(band) < 8192) band /= 2;
+    if (n <= 64) {
+        if (band == 32) return launch_search_t<64, 32>(s, z_pass, n, st);
+        return band == 16 ? launch_search_t<64, 16>(s, z_pass, n, st) : launch_search_t<64, 8>(s, z_pass, n, st);
+    }
+    if (n <= 128) {
+        if (band == 32) return launch_search_t<128, 32>(s, z_pass, n, st);
+        return band == 16 ? launch_search_t<128, 16>(s, z_pass, n, st) : launch_search_t<128, 8>(s, z_pass, n, st);
+    }
+    // at most 16 waves per work-group
+    if (n <= 256)
+        return band == 32 ? launch_search_t<256, 32>(s, z_pass, n, st) : launch_search_t<256, 16>(s, z_pass, n, st);
+    return launch_search_t<512, 32>(s, z_pass, n, st);
 }
 
 template <int TW, bool WIDE, int NTX>
 int launch_xy_w(const EdtMapSet& s, hipStream_t st)
 {
-    if (TW == 64 && NTX == 512 && !WIDE && lean_xy_ok(s)) {
-        int rc = launch_row_records(s, st);
-        if (rc) return rc;
-        // narrow stack entries (maps of at most 256 columns) fit twice the
-        // work-groups per CU but cost a little more per tile: they pay only
-        // when the launch has more tiles than the wide ones keep resident
-        // (2 per CU)
-        static int n_cu = 0;
-        if (!n_cu) {
-            int dev = 0, c = 0;
-            if (hipGetDevice(&dev) == hipSuccess &&
-                hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && c > 0)
-                n_cu = c;
-            else
-                n_cu = 256;
-        }
-        int nx_max = 0;
-        for (int i = 0; i < s.n; ++i) nx_max = std::max(nx_max, s.m[i].nx);
-        if (nx_max <= 256 && s.total > 2 * n_cu)
-            hipLaunchKernelGGL(k_edt_xy_lean<uint16_t>, dim3(s.total), dim3(512), 0, st, s);
-        else
-            hipLaunchKernelGGL(k_edt_xy_lean<uint32_t>, dim3(s.total), dim3(512), 0, st, s);
-        return check_launch("k_edt_xy_lean");
+    if (TW == 64 && NTX == 512 && !WIDE && search_xy_ok(s)) {
+        int rc = launch_row_records(s, true, st);
+        return rc ? rc : launch_search(s, false, st);
     }
     if (rows_first(s)) {
-        int rc = launch_row_records(s, st);
+        int rc = launch_row_records(s, false, st);
         if (rc) return rc;
         static bool done_rows = false;
         rc = allow_lds(k_edt_xy_rows<TW, WIDE, NTX>, done_rows);
@@ -218,9 +255,16 @@ int launch_xy_tw(const EdtMapSet& s, hipStream_t st)
 template <int TW, bool WIDE, int NTZ>
 int launch_z_t(const EdtMapSet& s, hipStream_t st)
 {
-    if (TW == 64 && NTZ == 256 && !WIDE && lean_z_ok(s)) {
-        hipLaunchKernelGGL(k_edt_z_lean, dim3(s.total), dim3(64 * ((s.nz_max + 31) / 32)), 0, st, s);
-        return check_launch("k_edt_z_lean");
+    if (TW == 64 && NTZ == 256 && !WIDE) {
+        // search tiles: 64 consecutive columns of the xy plane each
+        static thread_local EdtMapSet r;
+        r = s;
+        r.total = 0;
+        for (int i = 0; i < s.n; ++i) {
+            r.m[i].begin = r.total;
+            r.total += (s.m[i].nx * s.m[i].ny + 63) / 64;
+        }
+        return launch_search(r, true, st);
     }
     static bool done = false;
     int rc = allow_lds(k_edt_z<TW, WIDE, NTZ>, done);
@@ -303,10 +347,14 @@ EdtTuning default_tuning(const edt_grid_t* g)
     }
     t.z_tw = g->nz <= 128 ? 64 : (g->nz <= 256 ? 32 : 16);
     t.z_nt = 256;
-    // the lean tiles where they apply (64 / 512 for xy, 64 / 256 for z)
-    if (!needs_wide(g) && g->ny <= lean::XY_MAX && g->nx >= 64) {
-        t.xy_tw = 64;
-        t.xy_nt = 512;
+    // the search tiles (64 / 512 for xy, 64 / 256 for z) where they apply
+    if (!needs_wide(g)) {
+        if (search::records_fit(g->nx)) {
+            t.xy_tw = 64;
+            t.xy_nt = 512;
+        }
+        t.z_tw = 64;
+        t.z_nt = 256;
     }
     if (!tile_ok(1, t.xy_tw, g, t.xy_nt)) {
         t.xy_tw = 16;

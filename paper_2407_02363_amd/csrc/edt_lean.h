@@ -1,6 +1,6 @@
 #pragma once
-// Lean EDT tiles for the common map shapes (z <= 128 slices for the z pass,
-// y <= 256 rows for the xy pass, every axis <= 512): one wave per band, so
+// Lean EDT tiles of the persistent batched launch (z <= 128 slices for the z
+// pass, y <= 256 rows for the xy pass, every axis <= 512): one wave per band, so
 // the positions a wave visits are wave-uniform, and the band envelopes are
 // kept as per-lane masks of alive positions rather than as stacks.
 //

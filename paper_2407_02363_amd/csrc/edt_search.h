@@ -1,0 +1,435 @@
+#pragma once
+// EDT tiles by pruned search, for maps with every axis <= 512: the tiles
+// edt_compute and edt_compute_many use for such maps.
+//
+// Both passes minimise f_s(q) = h_s + (q - s)^2 over the sites s of a line
+// (Sec. III-C, steps 2-4), the smaller s on ties.  An envelope is built and
+// walked by one thread per line or band, a chain of dependent steps whose
+// length differs from lane to lane.  Here a wave (64 lanes = 64 lines) takes
+// blocks of 8 consecutive positions and evaluates every site that can win for
+// one of them, with no data-dependent chain:
+//
+//   * one packed integer (f_s(q) - i^2) << 9 | s per position q = qa + i, so
+//     that a minimum keeps the value and the smallest site at once; from one
+//     position to the next it changes by the lane-independent 2 (s - qa) << 9,
+//     and two sites cost 2 adds and one three-way minimum per position;
+//   * sites are skipped by bounds: every group (16 groups per line) and every
+//     chunk (C sites) keeps the smallest h of each lane, hmin.  hmin plus the
+//     squared distance between the far ends bounds every position's result
+//     from above, hmin plus the squared gap bounds what the chunk can offer
+//     from below, and a chunk is evaluated iff some lane's lower bound does
+//     not exceed its upper bound.  The result at the last position of the
+//     block before gives a second upper bound, and its site a lower limit
+//     (the winning site never decreases along a line).
+//
+// No stack and no merge: a line's sites are in LDS, a wave reads the ones it
+// evaluates, and each wave finishes its own band of BAND positions after a
+// single barrier.
+//
+// What bounds them is VALU issue: about 50 instructions per voxel and pass on
+// the benchmark's maps (17 to 35 evaluated sites per voxel at 1.75
+// instructions each, the bounds, the write-out).
+#include "edt_tiles.h"
+
+namespace edtmi {
+namespace search {
+
+using tiles::mul24;
+using tiles::XY_NONE;
+
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+constexpr int AXIS_MAX = 512;   // longest axis
+constexpr int NG = 16;          // groups per line
+constexpr int QB = 8;           // positions per block
+constexpr int SB = 9;           // bits of a site's position in a packed value
+// h of an empty position: above every real h + (q - s)^2 (at most 3 * 511^2 =
+// 783,363, 2 * 511^2 in the xy pass), and small enough that the packed value
+// stays below 2^31: at most 1,511^2 + 511^2 for V_EMPTY seen from any voxel,
+// + 511^2 for the position, below 2^22
+constexpr uint32_t V_EMPTY = 0xFC18u;   // x' = -1000, y' = 0
+constexpr int D_EMPTY = 1024;           // x - x' of an empty row
+constexpr int H_EMPTY = 1000000;        // every empty h is at least this
+static_assert(1511 * 1511 + 2 * 511 * 511 < (1 << (31 - SB)), "packed values must fit 31 bits");
+
+constexpr int W = 16;           // positions on either side of a block that the short test covers
+
+// ---------------------------------------------------------------------------
+// row records (step 1 once per row), 16 bytes per 64 columns of a row, in the
+// d2 buffer from its first 16-byte boundary on: the word (bit i = column
+// 64 w + i occupied) and the nearest occupied columns left and right of it
+// (-4096 and 8192 if none: farther than any real one).
+// ---------------------------------------------------------------------------
+constexpr int LEFT_NONE = -4096, RIGHT_NONE = 8192;
+
+struct Records {
+    uint4* r;
+    __device__ __forceinline__ void put(size_t i, uint64_t w, int left, int right) const
+    {
+        r[i] = make_uint4((uint32_t)w, (uint32_t)(w >> 32), (uint32_t)(left < 0 ? LEFT_NONE : left),
+                          (uint32_t)(right < 0 ? RIGHT_NONE : right));
+    }
+};
+
+__host__ __device__ inline Records records_of(int32_t* d2)
+{
+    return Records{reinterpret_cast<uint4*>(d2 + ((16u - ((unsigned)(uintptr_t)d2 & 15u)) & 15u) / 4u)};
+}
+
+// Rows of 8 voxels or more: 16 bytes per started 64 columns plus the
+// alignment fit into the row's 4 nx bytes of d2.
+__host__ __device__ inline bool records_fit(int nx) { return nx >= 8; }
+
+// Squared distances between block b (positions 8 b .. 8 b + 7) and group g of a
+// line: of their farthest and of their nearest ends.  Read with scalar loads.
+template <int NMAX> struct Bounds {
+    int far2[NMAX / QB][NG], gap2[NMAX / QB][NG];
+    constexpr Bounds() : far2{}, gap2{}
+    {
+        constexpr int G = NMAX / NG;
+        for (int b = 0; b < NMAX / QB; ++b)
+            for (int g = 0; g < NG; ++g) {
+                const int lo = G * g - QB * b;   // the group's first position, from the block's
+                const int f1 = lo + G - 1, f2 = QB - 1 - lo, far = f1 > f2 ? f1 : f2;
+                const int g1 = lo - (QB - 1), g2 = -(lo + G - 1), gap = g1 > g2 ? g1 : g2;
+                far2[b][g] = far * far;
+                gap2[b][g] = gap > 0 ? gap * gap : 0;
+            }
+    }
+};
+template <int NMAX> __constant__ constexpr Bounds<NMAX> BOUNDS{};
+
+__device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
+__device__ __forceinline__ bool any_lane2(bool p, bool q)
+{
+    return (__builtin_amdgcn_ballot_w64(p) & __builtin_amdgcn_ballot_w64(q)) != 0;
+}
+
+// ---------------------------------------------------------------------------
+// the search of one wave: positions [q0, q1) of its 64 lines
+//   np        positions with chunk minima (a multiple of BAND; the ones past
+//             the line's end are empty)
+//   cmin(c)   the smallest h of chunk c (this lane)
+//   site(c, k, a)  h of site k of chunk c, plus a (this lane)
+//   emit(q, n, value, s)  positions q .. q + n - 1 (n <= 8) of a line with
+//             sites: value[i] = f_s(q + i) for the winning site s[i]
+//   none(q)   a position of a line that has no site
+// ---------------------------------------------------------------------------
+template <int NMAX, int C, class CMin, class Site, class Emit, class None>
+__device__ __forceinline__ void search_band(int q0, int q1, int np, CMin cmin, Site site, Emit emit, None none)
+{
+    constexpr int G = NMAX / NG;
+    constexpr int CG = G / C;       // chunks per group
+    constexpr int CB = QB / C;      // chunks per block
+    constexpr int CW = W / C;       // chunks on either side of a block in the short test
+    int gm[NG];
+    auto group_min = [&](int g) {
+        int m = cmin(g * CG);
+#pragma unroll
+        for (int k = 1; k < CG; ++k) m = min(m, cmin(g * CG + k));
+        return m;
+    };
+    if (np == NMAX) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) gm[g] = group_min(g);
+    } else {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            gm[g] = 1 << 21;
+            if (g * G < np) gm[g] = group_min(g);
+        }
+    }
+    {
+        int m = gm[0];
+#pragma unroll
+        for (int g = 1; g < NG; ++g) m = min(m, gm[g]);
+        if (!any_lane(m < H_EMPTY)) {   // no site: a wave-wide fact
+            for (int q = q0; q < q1; ++q) none(q);
+            return;
+        }
+    }
+    const int nch = np / C;
+    int lo = 0;              // no site below lo can win from here on
+    int up = 0x7FFFFFFF;     // upper bound from the block before
+    for (int qa = q0; qa < q1; qa += QB) {
+        const int cb0 = qa / C;   // the block's first chunk
+        int best[QB];
+#pragma unroll
+        for (int i = 0; i < QB; ++i) best[i] = 0x7FFFFFFF;
+        auto evaluate = [&](int c) {
+            int p[C], st[C];
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const int sg = c * C + k - qa;
+                st[k] = sg << (SB + 1);
+                p[k] = (site(c, k, sg * sg) << SB) | (c * C + k);
+            }
+#pragma unroll
+            for (int k = 0; k < C; k += 2) {
+#pragma unroll
+                for (int i = 0; i < QB; ++i) {
+                    best[i] = min(min(best[i], p[k]), p[k + 1]);
+                    if (i + 1 < QB) {
+                        p[k] -= st[k];
+                        p[k + 1] -= st[k + 1];
+                    }
+                }
+            }
+        };
+        // ---- upper bound for every position of the block from its own
+        // chunks and the two beside them
+        int U = up;
+        U = min(U, cmin(cb0 > 0 ? cb0 - 1 : 0) + (C + QB - 1) * (C + QB - 1));
+        U = min(U, cmin(cb0 + CB < nch ? cb0 + CB : cb0) + (C + QB - 1) * (C + QB - 1));
+#pragma unroll
+        for (int k = 0; k < CB; ++k) U = min(U, cmin(cb0 + k) + (QB - 1) * (QB - 1));
+        if (!any_lane(U > W * W)) {
+            // nothing farther than W can win: the chunks up to there, directly
+            uint32_t cmask = 0;
+#pragma unroll
+            for (int j = 0; j < CB + 2 * CW; ++j) {
+                const int c = cb0 - CW + j;
+                const int gap = j < CW ? C * (CW - 1 - j) + 1 : (j < CW + CB ? 0 : C * (j - CW - CB) + 1);
+                const int m = cmin(c < 0 ? 0 : (c < nch ? c : nch - 1));
+                cmask |= any_lane2(m + gap * gap <= U, C * c + C - 1 >= lo) ? 1u << j : 0u;
+            }
+            cmask &= (cb0 < CW ? ~0u << (CW - cb0) : ~0u) &
+                     (nch - cb0 + CW < 32 ? (1u << (nch - cb0 + CW)) - 1u : ~0u);
+            while (cmask) {
+                evaluate(cb0 - CW + __builtin_ctz(cmask));
+                cmask &= cmask - 1u;
+            }
+        } else {
+            // the groups' bounds first, then the chunks of the groups left
+            const int* far2 = BOUNDS<NMAX>.far2[qa / QB];
+            const int* gap2 = BOUNDS<NMAX>.gap2[qa / QB];
+#pragma unroll
+            for (int g = 0; g < NG; ++g) U = min(U, gm[g] + far2[g]);
+            uint32_t gmask = 0;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) gmask |= any_lane(gm[g] + gap2[g] <= U) ? 1u << g : 0u;
+            while (gmask) {
+                const int g = __builtin_ctz(gmask);
+                gmask &= gmask - 1u;
+                uint32_t cmask = 0;
+#pragma unroll
+                for (int k = 0; k < CG; ++k) {
+                    const int c = g * CG + k;
+                    const int gap = c < cb0 ? C * (cb0 - c - 1) + 1 : (c < cb0 + CB ? 0 : C * (c - cb0) - (QB - 1));
+                    cmask |= any_lane2(cmin(c) + gap * gap <= U, C * c + C - 1 >= lo) ? 1u << k : 0u;
+                }
+                while (cmask) {
+                    evaluate(g * CG + __builtin_ctz(cmask));
+                    cmask &= cmask - 1u;
+                }
+            }
+        }
+        // ---- results
+        int val[QB], at[QB];
+#pragma unroll
+        for (int i = 0; i < QB; ++i) {
+            val[i] = (best[i] >> SB) + i * i;
+            at[i] = best[i] & (AXIS_MAX - 1);
+        }
+        // the last position's site s and value v bound the next block: f_s
+        // grows by 2 (q - s) + 1 from q to q + 1, and is convex along the block
+        lo = at[QB - 1];
+        const int d = qa + QB - 1 - lo;
+        up = max(val[QB - 1] + 2 * d + 1, val[QB - 1] + 2 * QB * d + QB * QB);
+        emit(qa, min(QB, q1 - qa), val, at);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// z pass (step 4): tile T = 64 consecutive columns of the map's xy plane (a
+// column's lane finds its x and y, so rows that are no multiple of 64 leave
+// no lane idle), one wave per band of BAND slices.  Reads the packed 2D sites
+// from site and overwrites d2 and site in place: every global read happens
+// before the barrier, every write after it, and a column belongs to one tile.
+//   lds   np * 256 bytes of sites [slice][lane], then np / C * 256 bytes of
+//         chunk minima, np = BAND * waves >= nz
+// ---------------------------------------------------------------------------
+template <int NMAX, int C, int BAND>
+__device__ __forceinline__ void z_tile(int32_t* __restrict__ d2, int32_t* __restrict__ site, int nx, int ny,
+                                       int nz, int T, int np, uint32_t* lds)
+{
+    uint32_t* val = lds;
+    int* cm = reinterpret_cast<int*>(lds + np * 64);
+    const int lane = threadIdx.x & 63;
+    const int band = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const unsigned plane = (unsigned)nx * (unsigned)ny;
+    const unsigned c0 = (unsigned)T * 64u;
+    const unsigned cc = min(c0 + lane, plane - 1u);
+    const bool live = c0 + lane < plane;
+    const unsigned y = cc / (unsigned)nx, x = cc - y * (unsigned)nx;
+    const s16x2 own = __builtin_bit_cast(s16x2, x | (y << 16));
+    const int q0 = band * BAND;
+    const int q1 = min(nz, q0 + BAND);
+    const unsigned off = cc - c0;
+    {
+        // all loads of the band in flight, clamped into the column
+        uint32_t v[BAND];
+        const uint32_t* in = reinterpret_cast<const uint32_t*>(site) + c0;
+#pragma unroll
+        for (int i = 0; i < BAND; ++i) v[i] = (in + (size_t)min(q0 + i, nz - 1) * plane)[off];
+        if (q0 + BAND > nz) {
+#pragma unroll
+            for (int i = 0; i < BAND; ++i)
+                if (q0 + i >= nz) v[i] = XY_NONE;
+        }
+        uint32_t* vb = val + q0 * 64 + lane;
+        int* cb = cm + q0 / C * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < BAND; i += C) {
+            int m = 1 << 21;
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const uint32_t e = v[i + k] == XY_NONE ? V_EMPTY : v[i + k];
+                vb[(i + k) * 64] = e;
+                const s16x2 d = own - __builtin_bit_cast(s16x2, e);
+                m = min(m, __builtin_amdgcn_sdot2(d, d, 0, false));
+            }
+            cb[i / C * 64] = m;
+        }
+    }
+    __syncthreads();
+    if (q0 >= q1) return;
+    const u16x2 lin = __builtin_bit_cast(u16x2, 1u | ((unsigned)nx << 16));
+    search_band<NMAX, C>(
+        q0, q1, np, [&](int c) { return cm[c * 64 + lane]; },
+        [&](int c, int k, int a) {
+            const s16x2 d = own - __builtin_bit_cast(s16x2, (val + c * (C * 64) + lane)[k * 64]);
+            return __builtin_amdgcn_sdot2(d, d, a, false);
+        },
+        [&](int q, int n, const int (&value)[QB], const int (&s)[QB]) {
+            int32_t lx[QB];   // x' + nx y' + plane z'
+#pragma unroll
+            for (int i = 0; i < QB; ++i)
+                lx[i] = (int32_t)__builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, val[s[i] * 64 + lane]), lin,
+                                                        __umul24(plane, (unsigned)s[i]), false);
+            if (!live) return;
+            int32_t* od = d2 + c0 + (size_t)q * plane;
+            int32_t* os = site + c0 + (size_t)q * plane;
+#pragma unroll
+            for (int i = 0; i < QB; ++i) {
+                if (i >= n) break;
+                od[off] = value[i];
+                os[off] = lx[i];
+                od += plane;
+                os += plane;
+            }
+        },
+        [&](int q) {
+            if (live) {
+                (d2 + c0 + (size_t)q * plane)[off] = 0x7FFFFFFF;
+                (site + c0 + (size_t)q * plane)[off] = -1;
+            }
+        });
+}
+
+// ---------------------------------------------------------------------------
+// xy pass (steps 2-3): tile T = z * ntx + x0 / 64, one wave per band of BAND
+// rows, from the map's row records.  Writes the 2D site x' | y' << 16 of every
+// voxel of the tile (0xFFFFFFFF if the slice is empty).
+//   lds   np * 128 bytes of x - x' [row][lane], then np / C * 128 bytes of
+//         chunk minima of |x - x'|, np = BAND * waves >= ny
+// ---------------------------------------------------------------------------
+// leading / trailing zeros, 0xFFFFFFFF for 0
+__device__ __forceinline__ uint32_t ffbh(uint32_t v)
+{
+    uint32_t r;
+    asm("v_ffbh_u32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+__device__ __forceinline__ uint32_t ffbl(uint32_t v)
+{
+    uint32_t r;
+    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
+template <int NMAX, int C, int BAND>
+__device__ __forceinline__ void xy_tile(const uint4* __restrict__ rec, uint32_t* __restrict__ out, int nx,
+                                        int ny, int ntx, int T, int np, uint32_t* lds)
+{
+    int16_t* dx = reinterpret_cast<int16_t*>(lds);
+    uint16_t* cm = reinterpret_cast<uint16_t*>(dx + np * 64);
+    const int lane = threadIdx.x & 63;
+    const int band = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int z = T / ntx;
+    const int tx = T - z * ntx;
+    // a lane past the row's end does what the row's last column does
+    const int bit = min(lane, nx - 1 - tx * 64);
+    const int xc = tx * 64 + bit;
+    const bool live = bit == lane;
+    const int nw = (nx + 63) >> 6;
+    const int q0 = band * BAND;
+    const int q1 = min(ny, q0 + BAND);
+    {
+        // lane r holds the record of row q0 + r, broadcast row by row
+        uint4 mine = make_uint4(0u, 0u, (uint32_t)LEFT_NONE, (uint32_t)RIGHT_NONE);
+        if (lane < BAND && q0 + lane < q1) mine = rec[((size_t)z * ny + q0 + lane) * nw + tx];
+        int16_t* db = dx + q0 * 64 + lane;
+        uint16_t* cb = cm + q0 / C * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < BAND; i += C) {
+            int m = D_EMPTY;
+#pragma unroll
+            for (int k = 0; k < C; ++k) {
+                const uint32_t wl = __builtin_amdgcn_readlane(mine.x, i + k);
+                const uint32_t wh = __builtin_amdgcn_readlane(mine.y, i + k);
+                const int l = (int)__builtin_amdgcn_readlane(mine.z, i + k);
+                const int r = (int)__builtin_amdgcn_readlane(mine.w, i + k);
+                int d = D_EMPTY;
+                if ((wl | wh) != 0 || l >= 0 || r < RIGHT_NONE) {   // wave-uniform
+                    // step 1: the nearest occupied column, ties to the left
+                    const uint64_t w = (uint64_t)wl | ((uint64_t)wh << 32);
+                    const uint64_t a = w << (63 - bit), b = w >> bit;
+                    const uint32_t dl = min(min(ffbh((uint32_t)(a >> 32)),
+                                                __builtin_elementwise_add_sat(ffbh((uint32_t)a), 32u)),
+                                            (uint32_t)(xc - l));
+                    const uint32_t dr = min(min(ffbl((uint32_t)b),
+                                                __builtin_elementwise_add_sat(ffbl((uint32_t)(b >> 32)), 32u)),
+                                            (uint32_t)(r - xc));
+                    d = dl <= dr ? (int)dl : -(int)dr;
+                    m = min(m, (int)min(dl, dr));
+                }
+                db[(i + k) * 64] = (int16_t)d;
+            }
+            cb[i / C * 64] = (uint16_t)m;
+        }
+    }
+    __syncthreads();
+    if (q0 >= q1) return;
+    uint32_t* o = out + (size_t)z * ny * nx + tx * 64;
+    search_band<NMAX, C>(
+        q0, q1, np,
+        [&](int c) {
+            const int m = cm[c * 64 + lane];
+            return mul24(m, m);
+        },
+        [&](int c, int k, int a) {
+            const int d = (dx + c * (C * 64) + lane)[k * 64];
+            return mul24(d, d) + a;
+        },
+        [&](int q, int n, const int (&)[QB], const int (&s)[QB]) {
+            uint32_t w[QB];
+#pragma unroll
+            for (int i = 0; i < QB; ++i) w[i] = (uint32_t)(xc - dx[s[i] * 64 + lane]) | ((uint32_t)s[i] << 16);
+            if (!live) return;
+            uint32_t* ow = o + (size_t)q * nx;
+#pragma unroll
+            for (int i = 0; i < QB; ++i) {
+                if (i >= n) break;
+                ow[lane] = w[i];
+                ow += nx;
+            }
+        },
+        [&](int q) {
+            if (live) (o + (size_t)q * nx)[lane] = XY_NONE;
+        });
+}
+
+}  // namespace search
+}  // namespace edtmi
