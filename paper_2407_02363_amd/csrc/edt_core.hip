@@ -42,8 +42,7 @@ __global__ __launch_bounds__(NTX) void k_edt_xy(EdtMapSet s)
 
 // Row records (step 1) of every map of the set: each wave takes
 // record_rows_per_wave(nx) whole rows of one map, four waves per work-group;
-// s.m[i].begin is the map's first wave.  SEARCH: in the search tiles' format.
-template <bool SEARCH>
+// s.m[i].begin is the map's first wave.
 __global__ __launch_bounds__(256) void k_row_records(EdtMapSet s)
 {
     const int wv = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
@@ -53,12 +52,10 @@ __global__ __launch_bounds__(256) void k_row_records(EdtMapSet s)
     const int per = record_rows_per_wave(d.occ, d.nx);
     const int row0 = (wv - d.begin) * per;
     const int nrows = min(per, d.ny * d.nz - row0);
-    auto run = [&](const auto& rec) {
-        if (record_words(d.occ, d.nx)) row_summary_words(d.occ, d.nx, (size_t)row0, nrows, rec);
-        else row_summary(d.occ, d.nx, (size_t)row0, nrows, rec);
-    };
-    if constexpr (SEARCH) run(search::records_of(d.d2));
-    else run(row_records(d.d2, d.nx, d.ny, d.nz));
+    if (record_words(d.occ, d.nx))
+        row_summary_words(d.occ, d.nx, (size_t)row0, nrows, row_records(d.d2, d.nx, d.ny, d.nz));
+    else
+        row_summary(d.occ, d.nx, (size_t)row0, nrows, row_records(d.d2, d.nx, d.ny, d.nz));
 }
 
 // Steps 2-3 from the row records.
@@ -93,6 +90,18 @@ __global__ __launch_bounds__(NTZ) void k_edt_z(EdtMapSet s)
 __device__ __forceinline__ const EdtMap& tile_map(const EdtMap& m, int) { return m; }
 __device__ __forceinline__ const EdtMap& tile_map(const EdtMapSet& s, int T) { return s.m[map_of(s, T)]; }
 
+// Occupancy bits of every map, 256 words per work-group (d.begin: the map's
+// first work-group).
+template <class Set>
+__global__ __launch_bounds__(256) void k_map_bits(Set s)
+{
+    const int B = (int)blockIdx.x;
+    const EdtMap& d = tile_map(s, B);
+    if (gated_off(d)) return;
+    search::map_bits(d.occ, (int64_t)d.nx * d.ny * d.nz, (int64_t)(B - d.begin) * 256 + threadIdx.x,
+                     reinterpret_cast<uint32_t*>(d.d2));
+}
+
 template <int NMAX, int C, int BAND, class Set>
 __global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_z_search(Set s, int waves)
 {
@@ -111,8 +120,9 @@ __global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_xy_search(Set s, int w
     const int T = xcd_chunk_remap(blockIdx.x, gridDim.x, 16);
     const EdtMap& d = tile_map(s, T);
     if (gated_off(d)) return;
-    search::xy_tile<NMAX, C, BAND>(search::records_of(d.d2).r, reinterpret_cast<uint32_t*>(d.site), d.nx, d.ny,
-                                   d.ntx, T - d.begin, BAND * waves, lds);
+    search::xy_tile<NMAX, C, BAND>(reinterpret_cast<const uint32_t*>(d.d2), search::misalignment(d.occ),
+                                   reinterpret_cast<uint32_t*>(d.site), d.nx, d.ny, d.ntx, T - d.begin,
+                                   BAND * waves, lds);
 }
 
 // Allow dynamic LDS beyond the 64 KiB default (gfx950 has 160 KiB per
@@ -142,18 +152,18 @@ bool rows_first(const EdtMapSet& s)
     return true;
 }
 
-// The search tiles take maps with every axis <= 512; the xy ones keep their
-// row records in d2.
+// The search tiles take maps with every axis <= 512; the xy ones keep the
+// occupancy bits in d2.
 bool search_xy_ok(const EdtMapSet& s)
 {
     if (s.wide) return false;
     for (int i = 0; i < s.n; ++i)
-        if (!search::records_fit(s.m[i].nx) || !s.m[i].d2) return false;
+        if (!s.m[i].d2 || !search::bits_fit((int64_t)s.m[i].nx * s.m[i].ny * s.m[i].nz)) return false;
     return true;
 }
 
 // Step 1 of every map of the set once per row, into the maps' d2 buffers.
-int launch_row_records(const EdtMapSet& s, bool search, hipStream_t st)
+int launch_row_records(const EdtMapSet& s, hipStream_t st)
 {
     static thread_local EdtMapSet r;   // the maps counted in waves (2.3 KiB: off the stack)
     r = s;
@@ -164,9 +174,24 @@ int launch_row_records(const EdtMapSet& s, bool search, hipStream_t st)
         waves += (s.m[i].ny * s.m[i].nz + per - 1) / per;
     }
     r.total = waves;
-    if (search) hipLaunchKernelGGL(k_row_records<true>, dim3((waves + 3) / 4), dim3(256), 0, st, r);
-    else hipLaunchKernelGGL(k_row_records<false>, dim3((waves + 3) / 4), dim3(256), 0, st, r);
+    hipLaunchKernelGGL(k_row_records, dim3((waves + 3) / 4), dim3(256), 0, st, r);
     return check_launch("k_row_records");
+}
+
+// The occupancy bits of every map of the set, into the maps' d2 buffers.
+int launch_map_bits(const EdtMapSet& s, hipStream_t st)
+{
+    static thread_local EdtMapSet r;
+    r = s;
+    int blocks = 0;
+    for (int i = 0; i < s.n; ++i) {
+        const int64_t n = (int64_t)s.m[i].nx * s.m[i].ny * s.m[i].nz + search::misalignment(s.m[i].occ);
+        r.m[i].begin = blocks;
+        blocks += (int)((n + 32 * 256 - 1) / (32 * 256));
+    }
+    if (s.n == 1) hipLaunchKernelGGL(k_map_bits<EdtMap>, dim3(blocks), dim3(256), 0, st, r.m[0]);
+    else hipLaunchKernelGGL(k_map_bits<EdtMapSet>, dim3(blocks), dim3(256), 0, st, r);
+    return check_launch("k_map_bits");
 }
 
 // One pass of the search tiles; n = the longest line of the pass.
@@ -225,11 +250,11 @@ template <int TW, bool WIDE, int NTX>
 int launch_xy_w(const EdtMapSet& s, hipStream_t st)
 {
     if (TW == 64 && NTX == 512 && !WIDE && search_xy_ok(s)) {
-        int rc = launch_row_records(s, true, st);
+        int rc = launch_map_bits(s, st);
         return rc ? rc : launch_search(s, false, st);
     }
     if (rows_first(s)) {
-        int rc = launch_row_records(s, false, st);
+        int rc = launch_row_records(s, st);
         if (rc) return rc;
         static bool done_rows = false;
         rc = allow_lds(k_edt_xy_rows<TW, WIDE, NTX>, done_rows);
@@ -349,7 +374,7 @@ EdtTuning default_tuning(const edt_grid_t* g)
     t.z_nt = 256;
     // the search tiles (64 / 512 for xy, 64 / 256 for z) where they apply
     if (!needs_wide(g)) {
-        if (search::records_fit(g->nx)) {
+        if (search::bits_fit(grid_voxels(g))) {
             t.xy_tw = 64;
             t.xy_nt = 512;
         }

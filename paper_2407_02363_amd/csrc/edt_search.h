@@ -46,40 +46,61 @@ constexpr int QB = 8;           // positions per block
 constexpr int SB = 9;           // bits of a site's position in a packed value
 // h of an empty position: above every real h + (q - s)^2 (at most 3 * 511^2 =
 // 783,363, 2 * 511^2 in the xy pass), and small enough that the packed value
-// stays below 2^31: at most 1,511^2 + 511^2 for V_EMPTY seen from any voxel,
-// + 511^2 for the position, below 2^22
+// stays below 2^31: at most 1,511^2 + 511^2 for V_EMPTY seen from any voxel and
+// 1,535^2 in the xy pass, + 511^2 for the position, below 2^22
 constexpr uint32_t V_EMPTY = 0xFC18u;   // x' = -1000, y' = 0
-constexpr int D_EMPTY = 1024;           // x - x' of an empty row
+constexpr int LEFT_NONE = -1024, RIGHT_NONE = 2047;   // x' where a row has none on that side:
+                                                      // the left one is the nearer, 1,024 .. 1,535 away
+constexpr int D_EMPTY = 1024;           // x - x' of rows past the map's
 constexpr int H_EMPTY = 1000000;        // every empty h is at least this
-static_assert(1511 * 1511 + 2 * 511 * 511 < (1 << (31 - SB)), "packed values must fit 31 bits");
+static_assert(1511 * 1511 + 2 * 511 * 511 < (1 << (31 - SB)) && 1535 * 1535 + 511 * 511 < (1 << (31 - SB)),
+              "packed values must fit 31 bits");
 
 constexpr int W = 16;           // positions on either side of a block that the short test covers
 
 // ---------------------------------------------------------------------------
-// row records (step 1 once per row), 16 bytes per 64 columns of a row, in the
-// d2 buffer from its first 16-byte boundary on: the word (bit i = column
-// 64 w + i occupied) and the nearest occupied columns left and right of it
-// (-4096 and 8192 if none: farther than any real one).
+// occupancy bits (the input of step 1): bit mis + lin = voxel lin is occupied,
+// mis = the occupancy pointer's offset from a 16-byte boundary.  They live in
+// the d2 buffer, which the xy pass does not use and the z pass overwrites.
 // ---------------------------------------------------------------------------
-constexpr int LEFT_NONE = -4096, RIGHT_NONE = 8192;
+// Words written plus the ones a row's last reads may touch, in a d2 of n words.
+__host__ __device__ inline bool bits_fit(int64_t n) { return n >= 16; }
 
-struct Records {
-    uint4* r;
-    __device__ __forceinline__ void put(size_t i, uint64_t w, int left, int right) const
-    {
-        r[i] = make_uint4((uint32_t)w, (uint32_t)(w >> 32), (uint32_t)(left < 0 ? LEFT_NONE : left),
-                          (uint32_t)(right < 0 ? RIGHT_NONE : right));
-    }
-};
+__host__ __device__ inline int misalignment(const void* occ) { return (int)((uintptr_t)occ & 15u); }
 
-__host__ __device__ inline Records records_of(int32_t* d2)
+// 0x80 in every byte of w that is not zero
+__device__ __forceinline__ uint32_t nonzero_high(uint32_t w)
 {
-    return Records{reinterpret_cast<uint4*>(d2 + ((16u - ((unsigned)(uintptr_t)d2 & 15u)) & 15u) / 4u)};
+    return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u;
 }
 
-// Rows of 8 voxels or more: 16 bytes per started 64 columns plus the
-// alignment fit into the row's 4 nx bytes of d2.
-__host__ __device__ inline bool records_fit(int nx) { return nx >= 8; }
+// 32 voxels per thread: bytes [32 u, 32 u + 32) from the 16-byte boundary at
+// or below occ.  A word that sticks out of the map is read byte by byte, so no
+// load leaves [occ, occ + n).
+__device__ __forceinline__ void map_bits(const uint8_t* __restrict__ occ, int64_t n, int64_t u,
+                                         uint32_t* __restrict__ bits)
+{
+    const int mis = misalignment(occ);
+    const int64_t f = 32 * u - mis;   // the word's first voxel
+    if (f >= n) return;
+    uint32_t m = 0;
+    if (f >= 0 && f + 32 <= n) {
+        const uint4* p = reinterpret_cast<const uint4*>(occ + f);
+        const uint4 a = p[0], b = p[1];
+        const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            // the eight 0x80 flags of two words, weighted 1 .. 128: 128 times their bits
+            uint32_t t = __builtin_amdgcn_udot4(nonzero_high(w[2 * k]), 0x08040201u, 0u, false);
+            t = __builtin_amdgcn_udot4(nonzero_high(w[2 * k + 1]), 0x80402010u, t, false);
+            m |= (t >> 7) << (8 * k);
+        }
+    } else {
+        for (int k = 0; k < 32; ++k)
+            if (f + k >= 0 && f + k < n && occ[f + k]) m |= 1u << k;
+    }
+    bits[u] = m;
+}
 
 // Squared distances between block b (positions 8 b .. 8 b + 7) and group g of a
 // line: of their farthest and of their nearest ends.  Read with scalar loads.
@@ -330,8 +351,8 @@ __device__ __forceinline__ void z_tile(int32_t* __restrict__ d2, int32_t* __rest
 
 // ---------------------------------------------------------------------------
 // xy pass (steps 2-3): tile T = z * ntx + x0 / 64, one wave per band of BAND
-// rows, from the map's row records.  Writes the 2D site x' | y' << 16 of every
-// voxel of the tile (0xFFFFFFFF if the slice is empty).
+// rows, from the map's occupancy bits.  Writes the 2D site x' | y' << 16 of
+// every voxel of the tile (0xFFFFFFFF if the slice is empty).
 //   lds   np * 128 bytes of x - x' [row][lane], then np / C * 128 bytes of
 //         chunk minima of |x - x'|, np = BAND * waves >= ny
 // ---------------------------------------------------------------------------
@@ -350,8 +371,8 @@ __device__ __forceinline__ uint32_t ffbl(uint32_t v)
 }
 
 template <int NMAX, int C, int BAND>
-__device__ __forceinline__ void xy_tile(const uint4* __restrict__ rec, uint32_t* __restrict__ out, int nx,
-                                        int ny, int ntx, int T, int np, uint32_t* lds)
+__device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int mis, uint32_t* __restrict__ out,
+                                        int nx, int ny, int ntx, int T, int np, uint32_t* lds)
 {
     int16_t* dx = reinterpret_cast<int16_t*>(lds);
     uint16_t* cm = reinterpret_cast<uint16_t*>(dx + np * 64);
@@ -363,39 +384,70 @@ __device__ __forceinline__ void xy_tile(const uint4* __restrict__ rec, uint32_t*
     const int bit = min(lane, nx - 1 - tx * 64);
     const int xc = tx * 64 + bit;
     const bool live = bit == lane;
-    const int nw = (nx + 63) >> 6;
     const int q0 = band * BAND;
     const int q1 = min(ny, q0 + BAND);
     {
-        // lane r holds the record of row q0 + r, broadcast row by row
-        uint4 mine = make_uint4(0u, 0u, (uint32_t)LEFT_NONE, (uint32_t)RIGHT_NONE);
-        if (lane < BAND && q0 + lane < q1) mine = rec[((size_t)z * ny + q0 + lane) * nw + tx];
+        // lane r takes row q0 + r: the tile's 64-column word and the nearest
+        // occupied columns left and right of it, from the row's words (each
+        // cut out of the bits with funnel shifts)
+        constexpr int NW = AXIS_MAX / 64;
+        uint32_t wl = 0, wh = 0;
+        int l = LEFT_NONE, r = RIGHT_NONE;
+        if (lane < BAND && q0 + lane < q1) {
+            const unsigned b = ((unsigned)z * ny + q0 + lane) * nx + mis;
+            const uint32_t* p = bits + (b >> 5);
+            uint32_t d[2 * NW + 1];
+#pragma unroll
+            for (int i = 0; i <= 2 * NW; ++i)
+                if (i <= 2 * ntx) d[i] = p[i];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if (w >= ntx) break;
+                uint32_t a = __builtin_amdgcn_alignbit(d[2 * w + 1], d[2 * w], b);
+                uint32_t c = __builtin_amdgcn_alignbit(d[2 * w + 2], d[2 * w + 1], b);
+                const int valid = nx - 64 * w;   // columns past the row's end
+                if (valid < 64) {
+                    a &= valid < 32 ? (1u << valid) - 1u : ~0u;
+                    c &= valid > 32 ? (1u << (valid - 32)) - 1u : 0u;
+                }
+                if (w < tx) {
+                    if (a | c) l = 64 * w + (c ? 63 - __builtin_clz(c) : 31 - __builtin_clz(a));
+                } else if (w == tx) {
+                    wl = a;
+                    wh = c;
+                } else if (r == RIGHT_NONE) {
+                    if (a | c) r = 64 * w + (a ? __builtin_ctz(a) : 32 + __builtin_ctz(c));
+                }
+            }
+        }
+        const uint64_t rows = __builtin_amdgcn_ballot_w64((wl | wh) != 0 || l >= 0 || r < RIGHT_NONE);
+        const uint32_t lr = ((uint32_t)l & 0xFFFFu) | ((uint32_t)r << 16);
         int16_t* db = dx + q0 * 64 + lane;
         uint16_t* cb = cm + q0 / C * 64 + lane;
 #pragma unroll
         for (int i = 0; i < BAND; i += C) {
-            int m = D_EMPTY;
+            if (((rows >> i) & ((1u << C) - 1u)) == 0) {   // wave-uniform
+#pragma unroll
+                for (int k = 0; k < C; ++k) db[(i + k) * 64] = (int16_t)D_EMPTY;
+                cb[i / C * 64] = (uint16_t)D_EMPTY;
+                continue;
+            }
+            uint32_t m = 2 * D_EMPTY;
 #pragma unroll
             for (int k = 0; k < C; ++k) {
-                const uint32_t wl = __builtin_amdgcn_readlane(mine.x, i + k);
-                const uint32_t wh = __builtin_amdgcn_readlane(mine.y, i + k);
-                const int l = (int)__builtin_amdgcn_readlane(mine.z, i + k);
-                const int r = (int)__builtin_amdgcn_readlane(mine.w, i + k);
-                int d = D_EMPTY;
-                if ((wl | wh) != 0 || l >= 0 || r < RIGHT_NONE) {   // wave-uniform
-                    // step 1: the nearest occupied column, ties to the left
-                    const uint64_t w = (uint64_t)wl | ((uint64_t)wh << 32);
-                    const uint64_t a = w << (63 - bit), b = w >> bit;
-                    const uint32_t dl = min(min(ffbh((uint32_t)(a >> 32)),
-                                                __builtin_elementwise_add_sat(ffbh((uint32_t)a), 32u)),
-                                            (uint32_t)(xc - l));
-                    const uint32_t dr = min(min(ffbl((uint32_t)b),
-                                                __builtin_elementwise_add_sat(ffbl((uint32_t)(b >> 32)), 32u)),
-                                            (uint32_t)(r - xc));
-                    d = dl <= dr ? (int)dl : -(int)dr;
-                    m = min(m, (int)min(dl, dr));
-                }
-                db[(i + k) * 64] = (int16_t)d;
+                // step 1: the nearest occupied column of a row, ties to the left
+                const uint64_t w = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(wl, i + k) |
+                                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(wh, i + k) << 32);
+                const int s = __builtin_amdgcn_readlane(lr, i + k);
+                const uint64_t a = w << (63 - bit), b = w >> bit;
+                const uint32_t dl = min(min(ffbh((uint32_t)(a >> 32)),
+                                            __builtin_elementwise_add_sat(ffbh((uint32_t)a), 32u)),
+                                        (uint32_t)(xc - (int)(int16_t)s));
+                const uint32_t dr = min(min(ffbl((uint32_t)b),
+                                            __builtin_elementwise_add_sat(ffbl((uint32_t)(b >> 32)), 32u)),
+                                        (uint32_t)((s >> 16) - xc));
+                db[(i + k) * 64] = (int16_t)(dl <= dr ? (int)dl : -(int)dr);
+                m = min(m, min(dl, dr));
             }
             cb[i / C * 64] = (uint16_t)m;
         }

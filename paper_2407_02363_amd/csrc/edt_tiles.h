@@ -728,12 +728,6 @@ struct RowRecords {
     uint64_t* word;
     int16_t* left;
     int16_t* right;
-    __device__ __forceinline__ void put(size_t i, uint64_t w, int l, int r) const
-    {
-        word[i] = w;
-        left[i] = (int16_t)l;
-        right[i] = (int16_t)r;
-    }
 };
 
 __host__ __device__ inline RowRecords row_records(int32_t* d2, int nx, int ny, int nz)
@@ -778,9 +772,8 @@ __device__ __forceinline__ uint64_t spread4(uint64_t x)
 
 // Every word's nearest occupied columns outside it within its row, for the
 // words held by lanes [0, items), nw lanes per row, and the stores.
-template <class Rec>
 __device__ __forceinline__ void row_records_store(uint64_t mine, int items, int nw, size_t row0,
-                                                  const Rec& rec)
+                                                  const RowRecords& rec)
 {
     const int lane = (int)(threadIdx.x & 63);
     const uint64_t filled = __ballot(lane < items && mine != 0);
@@ -795,9 +788,12 @@ __device__ __forceinline__ void row_records_store(uint64_t mine, int items, int 
     const int qw = above ? __ffsll((unsigned long long)above) - 1 : 0;
     const uint64_t wl = __shfl(mine, pw);
     const uint64_t wr = __shfl(mine, qw);
-    if (lane < items)
-        rec.put(row0 * (size_t)nw + lane, mine, below ? 64 * (pw - s0) + 63 - __clzll(wl) : -1,
-                above ? 64 * (qw - s0) + __ffsll((unsigned long long)wr) - 1 : -1);
+    if (lane < items) {
+        const size_t i = row0 * (size_t)nw + lane;
+        rec.word[i] = mine;
+        rec.left[i] = (int16_t)(below ? 64 * (pw - s0) + 63 - __clzll(wl) : -1);
+        rec.right[i] = (int16_t)(above ? 64 * (qw - s0) + __ffsll((unsigned long long)wr) - 1 : -1);
+    }
 }
 
 // The records of rows [row0, row0 + nrows), 4 bytes per lane: load j is the
@@ -805,9 +801,8 @@ __device__ __forceinline__ void row_records_store(uint64_t mine, int items, int 
 // position gives, for each word of the chunk, every fourth bit.  Lane
 // r * nw + w keeps the four ballots of its load and interleaves them into
 // word w of row r.
-template <class Rec>
 __device__ __forceinline__ void row_summary_words(const uint8_t* __restrict__ occ, int nx, size_t row0,
-                                                  int nrows, const Rec& rec)
+                                                  int nrows, const RowRecords& rec)
 {
     const int lane = (int)(threadIdx.x & 63);
     const int nw = (nx + 63) >> 6, nch = (nx + 255) >> 8;
@@ -855,9 +850,8 @@ __device__ __forceinline__ void row_summary_words(const uint8_t* __restrict__ oc
 // ballot per item gives its word, kept by lane j.  A ballot of the non-empty
 // words and two shuffles give every word's nearest occupied columns outside
 // it within its row.
-template <class Rec>
 __device__ __forceinline__ void row_summary(const uint8_t* __restrict__ occ, int nx, size_t row0,
-                                            int nrows, const Rec& rec)
+                                            int nrows, const RowRecords& rec)
 {
     const int lane = (int)(threadIdx.x & 63);
     const int nw = (nx + 63) >> 6;      // 1..16
