@@ -7,19 +7,27 @@
 // fixed-point sums, so independent of the order of accumulation); keep i
 // iff d_i <= mu + alpha * sigma.
 //
-// Neighbour search: cells slightly larger than R / 2 (1.001 R / 2), so
-// every neighbour within R lies in the 5 x 5 x 5 cells around a point for
+// Neighbour search: cells slightly larger than R (1.001 R), so every
+// neighbour within R lies in the 3 x 3 x 3 cells around a point for
 // coordinates below about 80 m.  The table is the grid of cells wrapped onto
 // A x B x C buckets (powers of two, each at least 8): cells that differ by
-// whole periods share a bucket, the 125 cells around any cell fall into
+// whole periods share a bucket, the 27 cells around any cell fall into
 // distinct buckets, and the cells of an x run into consecutive ones.  Points
-// are counted per bucket, the counts are scanned into bucket offsets, and the
-// points are scattered into their buckets, so the points of an x run of
-// cells are one contiguous range (two where the run wraps).  A query visits
-// its own cell, then the 25 x runs nearest first, each trimmed to the cells
-// that can still hold one of the k nearest, with one thread per point in
-// bucket order.  The k smallest squared distances are kept sorted in
-// registers by a compare-exchange pass per candidate.
+// are counted per bucket, every bucket gets a place in the sorted points, and
+// the points are scattered there, so the points of an x run of cells are one
+// contiguous range (two where the run wraps).
+//
+// One thread per point in bucket order.  Read lane by lane from memory, the
+// candidates (about 90 a point, each lane at its own place) cost the texture
+// unit 80 cycles per load instruction, 205 us in all.  So a wave first copies
+// what its points need into LDS: its points lie in two or three rows of cells,
+// and the points of a row's x range in each of the nine rows around it are one
+// contiguous range.  Each lane then streams its own nine ranges from LDS four
+// candidates at a time, the next four in flight, and keeps the k smallest
+// squared distances sorted in registers, one median per kept value and
+// candidate.  307,200 points: 252 us with cells of R / 2 read from memory (26
+// runs, each two dependent loads and at least eight candidate slots), 82 us
+// like this.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -41,17 +49,16 @@ struct Wrap {
 };
 
 struct SorLayout {
-    size_t count, start, cursor, sums, spts, acc, total;
+    size_t count, table, spts, acc, total;
     unsigned tmask;
     Wrap wrap;
-    int nsums;
 };
 
-// table size: a power of two >= 4 n, at least 1024, at most 2^23
+// table size: a power of two >= 2 n, at least 1024, at most 2^23
 __host__ inline SorLayout sor_layout(int64_t n)
 {
     int64_t T = 1024;
-    while (T < 4 * n && T < (int64_t(1) << 23)) T <<= 1;
+    while (T < 2 * n && T < (int64_t(1) << 23)) T <<= 1;
     SorLayout L;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -60,17 +67,14 @@ __host__ inline SorLayout sor_layout(int64_t n)
         return at;
     };
     L.count = take((size_t)T * 4);
-    L.start = take((size_t)T * 4);
-    L.cursor = take((size_t)T * 4);
-    L.nsums = (int)(T / 1024);
-    L.sums = take((size_t)L.nsums * 4);
+    L.table = take((size_t)T * 8);
     L.spts = take((size_t)std::max<int64_t>(n, 1) * 16);
-    L.acc = take(4 * 8);
+    L.acc = take((size_t)(64 + 1) * 128);   // ACC_SLOTS lines and one more
     L.total = o;
     L.tmask = (unsigned)(T - 1);
     int t = 0;
     while ((int64_t(1) << t) < T) ++t;
-    // T >= 2^10, so A, B and C are each at least 8
+    // T >= 2^10, so A, B and C are each at least 8, and A is at most 256
     const int a = (t + 2) / 3, b = (t - a + 1) / 2, c = t - a - b;
     L.wrap.mx = (1u << a) - 1u;
     L.wrap.my = (1u << b) - 1u;
@@ -96,15 +100,48 @@ __device__ __forceinline__ unsigned bucket(int ix, int iy, int iz, const Wrap& w
     return ((unsigned)ix & w.mx) | (((unsigned)iy & w.my) << w.sy) | (((unsigned)iz & w.mz) << w.sz);
 }
 
-__global__ void k_sor_zero(unsigned* __restrict__ count, unsigned* __restrict__ cursor, int T,
-                           unsigned long long* __restrict__ acc)
+// The sums of d and d^2 and the finite points are kept in ACC_SLOTS places, a
+// cache line each, work-groups taking turns: on one line the 14,400 atomic
+// additions of a frame would take 200 us.  The line after them counts the
+// sorted points given out.
+constexpr int ACC_SLOTS = 64, ACC_LINE = 16;
+constexpr int ACC_GIVEN = ACC_SLOTS * ACC_LINE;
+
+__global__ void k_sor_zero(uint4* __restrict__ count, int T4, unsigned long long* __restrict__ acc)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < T) {
-        count[i] = 0u;
-        cursor[i] = 0u;
-    }
-    if (i < 4) acc[i] = 0ull;
+    if (i < T4) count[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (i <= ACC_GIVEN) acc[i] = 0ull;
+}
+
+// Neighbouring points of a frame tend to share a bucket, and atomics on one
+// address take turns: of every run of lanes with the same bucket (among the
+// active lanes of the wave, in lane order) the first lane acts for all n, and
+// rank is the lane's place in its run.
+struct Run {
+    bool first;
+    int n, rank, leader;
+};
+__device__ __forceinline__ Run same_bucket_run(unsigned b)
+{
+    const int lane = threadIdx.x & 63;
+    const uint64_t act = __ballot(1);
+    const uint64_t below = act & ((1ull << lane) - 1ull);
+    const int prev = below ? 63 - __clzll(below) : -1;
+    const unsigned pb = __shfl(b, prev < 0 ? lane : prev, 64);
+    const bool first = prev < 0 || pb != b;
+    const uint64_t heads = __ballot(first);
+    const uint64_t upto = heads & ((lane < 63 ? 1ull << (lane + 1) : 0ull) - 1ull);
+    const uint64_t after = heads & ~((lane < 63 ? 1ull << (lane + 1) : 0ull) - 1ull);
+    const int leader = 63 - __clzll(upto);
+    const int next = after ? __ffsll((unsigned long long)after) - 1 : 64;
+    const uint64_t from = ~0ull << leader;
+    Run r;
+    r.first = first;
+    r.leader = leader;
+    r.n = __popcll(act & from & (next < 64 ? (1ull << next) - 1ull : ~0ull));
+    r.rank = __popcll(act & from & ((1ull << lane) - 1ull));
+    return r;
 }
 
 // Counts the finite points per bucket; a point that is not finite gets its
@@ -119,72 +156,56 @@ __global__ void k_sor_count(const float* __restrict__ pts, int64_t n, float h, W
         dmean[i] = __builtin_nanf("");
         return;
     }
-    atomicAdd(count + bucket(cell_of(x, h), cell_of(y, h), cell_of(z, h), w), 1u);
+    const unsigned b = bucket(cell_of(x, h), cell_of(y, h), cell_of(z, h), w);
+    const Run r = same_bucket_run(b);
+    if (r.first) atomicAdd(count + b, (unsigned)r.n);
 }
 
-// exclusive scan of T counts (T a multiple of 1024): per-block scan of 1024
-// values (4 per thread), one block scanning the block totals, then the add
-__global__ __launch_bounds__(256) void k_scan_blocks(const unsigned* __restrict__ in,
-                                                     unsigned* __restrict__ out,
-                                                     unsigned* __restrict__ sums)
+// Places the buckets in the sorted points: {first point, points} per bucket.
+// A work-group scans 4096 consecutive buckets (whole x rows of cells) and
+// takes their points' places from a counter, so the order of the blocks
+// varies, but a row's buckets follow each other.
+constexpr int PLACE_PER = 4;                    // uint4 of counts per thread
+__global__ __launch_bounds__(256) void k_sor_place(const uint4* __restrict__ count, int T4,
+                                                   uint4* __restrict__ table,
+                                                   unsigned long long* __restrict__ acc)
 {
-    __shared__ unsigned s[256];
-    const int base = blockIdx.x * 1024 + 4 * threadIdx.x;
-    const uint4 v = *reinterpret_cast<const uint4*>(in + base);
-    const unsigned t = v.x + v.y + v.z + v.w;
-    s[threadIdx.x] = t;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const unsigned add = threadIdx.x >= (unsigned)off ? s[threadIdx.x - off] : 0u;
-        __syncthreads();
-        s[threadIdx.x] += add;
-        __syncthreads();
-    }
-    const unsigned ex = s[threadIdx.x] - t;
-    *reinterpret_cast<uint4*>(out + base) = make_uint4(ex, ex + v.x, ex + v.x + v.y, ex + v.x + v.y + v.z);
-    if (threadIdx.x == 255) sums[blockIdx.x] = s[255];
-}
-
-__global__ __launch_bounds__(1024) void k_scan_sums(unsigned* __restrict__ sums, int nb)
-{
-    __shared__ unsigned s[1024];
-    const int per = (nb + 1023) / 1024;
-    const int b0 = threadIdx.x * per;
+    __shared__ unsigned wsum[4], base;
+    const int i0 = (blockIdx.x * 256 + threadIdx.x) * PLACE_PER;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint4 v[PLACE_PER];
     unsigned t = 0;
-    for (int j = 0; j < per; ++j)
-        if (b0 + j < nb) t += sums[b0 + j];
-    s[threadIdx.x] = t;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const unsigned add = threadIdx.x >= (unsigned)off ? s[threadIdx.x - off] : 0u;
-        __syncthreads();
-        s[threadIdx.x] += add;
-        __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PLACE_PER; ++k) {
+        v[k] = i0 + k < T4 ? count[i0 + k] : make_uint4(0u, 0u, 0u, 0u);
+        t += v[k].x + v[k].y + v[k].z + v[k].w;
     }
-    unsigned run = s[threadIdx.x] - t;
-    for (int j = 0; j < per; ++j)
-        if (b0 + j < nb) {
-            const unsigned c = sums[b0 + j];
-            sums[b0 + j] = run;
-            run += c;
-        }
+    unsigned s = t;   // inclusive scan of the wave
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned u = __shfl_up(s, off, 64);
+        s += lane >= off ? u : 0u;
+    }
+    if (lane == 63) wsum[wave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        base = (unsigned)atomicAdd(acc + ACC_GIVEN, (unsigned long long)(wsum[0] + wsum[1] + wsum[2] + wsum[3]));
+    __syncthreads();
+    unsigned first = base + s - t;
+    for (int k = 0; k < wave; ++k) first += wsum[k];
+#pragma unroll
+    for (int k = 0; k < PLACE_PER; ++k) {
+        if (i0 + k >= T4) break;
+        const unsigned a = first, b = a + v[k].x, c = b + v[k].y, d = c + v[k].z;
+        table[2 * (i0 + k)] = make_uint4(a, v[k].x, b, v[k].y);
+        table[2 * (i0 + k) + 1] = make_uint4(c, v[k].z, d, v[k].w);
+        first = d + v[k].w;
+    }
 }
 
-__global__ __launch_bounds__(256) void k_scan_add(unsigned* __restrict__ out,
-                                                  const unsigned* __restrict__ sums)
-{
-    const unsigned add = sums[blockIdx.x];
-    uint4* p = reinterpret_cast<uint4*>(out + blockIdx.x * 1024 + 4 * threadIdx.x);
-    uint4 v = *p;
-    v.x += add;
-    v.y += add;
-    v.z += add;
-    v.w += add;
-    *p = v;
-}
-
+// Takes the places of a bucket from its last one down: count is used up.
 __global__ void k_sor_scatter(const float* __restrict__ pts, int64_t n, float h, Wrap w,
-                              const unsigned* __restrict__ start, unsigned* __restrict__ cursor,
+                              const uint2* __restrict__ table, unsigned* __restrict__ count,
                               float4* __restrict__ spts)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -192,8 +213,11 @@ __global__ void k_sor_scatter(const float* __restrict__ pts, int64_t n, float h,
     const float x = pts[3 * i], y = pts[3 * i + 1], z = pts[3 * i + 2];
     if (!finite3(x, y, z)) return;
     const unsigned b = bucket(cell_of(x, h), cell_of(y, h), cell_of(z, h), w);
-    const unsigned pos = start[b] + atomicAdd(cursor + b, 1u);
-    spts[pos] = make_float4(x, y, z, __int_as_float((int)i));
+    const Run r = same_bucket_run(b);
+    unsigned left = 0;   // points of the bucket still to place before the run's
+    if (r.first) left = atomicSub(count + b, (unsigned)r.n);
+    left = __shfl(left, r.leader, 64);
+    spts[table[b].x + left - 1u - (unsigned)r.rank] = make_float4(x, y, z, __int_as_float((int)i));
 }
 
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
@@ -205,126 +229,197 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
 
 // One thread per finite point, points in bucket order (neighbouring cells
 // sit side by side in spts, so a wave's points share candidate ranges).  A
-// query visits its own cell, then the 25 x runs (dy, dz in -2..2) of the
-// 5 x 5 x 5 cells around it, nearest first, each run a contiguous range of
-// cells dx in lo..hi (its own cell left out of the own run).  That is exact:
-// a point within R lies in one of the 125 cells, whose ranges are disjoint,
-// so it is counted once; candidates from cells a whole period away lie
-// farther than R and fail the radius test.  Once k neighbours are in hand, a
-// cell whose box (widened by a rounding slack) lies farther than the current
-// k-th nearest is left out: its points cannot change the k smallest
-// distances, and the count m = min(found, k) is already k.  The visiting
-// order changes nothing: the k smallest values are summed in ascending
+// query takes the nine x runs (dy, dz in -1..1) of the 3 x 3 x 3 cells around
+// it.  That is exact: a point within R lies in one of the 27 cells, whose
+// ranges are disjoint, so it is counted once; candidates from cells a whole
+// period away lie farther than R and fail the radius test.  Once k neighbours
+// are in hand, a run whose cells (widened by a rounding slack) lie farther than
+// the current k-th nearest is left out: its points cannot change the k
+// smallest distances, and the count m = min(found, k) is already k.  The
+// visiting order changes nothing: the k smallest values are summed in ascending
 // order, and the statistics are integer sums, reduced per wave before one
 // atomic add per wave.
+// Points a wave's LDS holds; a wave that needs more reads from memory.  307,200
+// points, the whole filter: 116-124 us with 768, 131 with 1024, 148 with 1536 (fewer
+// waves per CU).
+constexpr int CAP = 768;
+static_assert(3 * CAP >= 36 * 64, "18 ranges per lane");
+
 template <int K>
-__global__ __launch_bounds__(256) void k_sor_knn(int k, float R, float h, Wrap w, unsigned T,
-                                                 const unsigned* __restrict__ start,
-                                                 const unsigned* __restrict__ count,
-                                                 const float4* __restrict__ spts,
-                                                 float* __restrict__ dmean,
-                                                 unsigned long long* __restrict__ acc)
+__global__ __launch_bounds__(64) void k_sor_knn(int k, float R, float h, Wrap w,
+                                                const uint2* __restrict__ table,
+                                                const float4* __restrict__ spts,
+                                                float* __restrict__ dmean,
+                                                unsigned long long* __restrict__ acc)
 {
-    const unsigned t = blockIdx.x * blockDim.x + threadIdx.x;
-    const unsigned nfin = start[T - 1] + count[T - 1];
+    // x, y and z of the wave's points; later a lane's ranges in spts
+    __shared__ uint32_t buf[3 * CAP];
+    __shared__ uint32_t ranges[9][64];   // a lane's non-empty ranges in buf: first | end << 16
+    uint32_t *sx = buf, *sy = buf + CAP, *sz = buf + 2 * CAP;
+    const int lane = threadIdx.x;
+    const unsigned t = blockIdx.x * 64u + lane;
+    const unsigned nfin = (unsigned)acc[ACC_GIVEN];
+    const bool active = t < nfin;
     unsigned long long a1 = 0, a2 = 0, a3 = 0;
-    if (t < nfin) {
-        const float4 P = spts[t];
-        const int i = __float_as_int(P.w);
-        const float px = P.x, py = P.y, pz = P.z;
-        const float rr = R * R;
-        const int cx = cell_of(px, h), cy = cell_of(py, h), cz = cell_of(pz, h);
-        // a point's cell can differ from its coordinates' box by rounding;
-        // the pruning bound below is shrunk by this slack
-        const float slack = 1e-4f * h + 1e-6f * (fabsf(px) + fabsf(py) + fabsf(pz));
+    const float4 P = active ? spts[t] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int i = __float_as_int(P.w);
+    const float px = P.x, py = P.y, pz = P.z;
+    const float rr = R * R;
+    const int cx = cell_of(px, h), cy = cell_of(py, h), cz = cell_of(pz, h);
+    // the x run in bucket coordinates; where it wraps round the table, the
+    // cell on the other side is left for later
+    const unsigned xw = (unsigned)cx & w.mx;
+    const unsigned xs = xw > 0 ? xw - 1 : 0, xe = min(xw + 1, w.mx);
+    constexpr int RY[9] = {0, -1, 1, 0, 0, -1, 1, -1, 1}, RZ[9] = {0, 0, 0, -1, 1, -1, -1, 1, 1};
+    unsigned e0[9], e1[9];
+#pragma unroll
+    for (int r = 0; r < 9; ++r) {
+        e0[r] = e1[r] = 0;
+        if (active) {
+            const unsigned row = bucket(0, cy + RY[r], cz + RZ[r], w);
+            e0[r] = table[row | xs].x;
+            const uint2 c = table[row | xe];
+            e1[r] = c.x + c.y;
+        }
+    }
+    // ---- the wave's candidates into LDS: for every row of cells that its
+    // lanes lie in (consecutive lanes, ascending x), the nine rows around it from
+    // the first lane's first cell to the last lane's last
+    const unsigned key = bucket(0, cy, cz, w);
+    int used = 0, nr = 0, self = 0;
+    bool fits = true;
+    for (uint64_t todo = __ballot(active); todo && fits;) {
+        const int first = __ffsll((unsigned long long)todo) - 1;
+        const unsigned gk = __builtin_amdgcn_readlane(key, first);
+        const bool mine = active && key == gk;
+        const uint64_t grp = __ballot(mine) & todo;
+        const int last = 63 - __clzll(grp);
+        todo &= ~grp;
+        unsigned s0[9];
+        int len[9], total = 0;
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            s0[r] = __builtin_amdgcn_readlane(e0[r], first);
+            const unsigned n = (unsigned)__builtin_amdgcn_readlane(e1[r], last) - s0[r];
+            len[r] = (int)min(n, (unsigned)CAP + 1u);
+            total += len[r];
+        }
+        if (used + total > CAP) {
+            fits = false;
+            break;
+        }
+        float4 q[9];
+#pragma unroll
+        for (int r = 0; r < 9; ++r)
+            if (lane < len[r]) q[r] = spts[s0[r] + lane];
+#pragma unroll
+        for (int r = 0; r < 9; ++r) {
+            if (lane < len[r]) {
+                sx[used + lane] = __float_as_uint(q[r].x);
+                sy[used + lane] = __float_as_uint(q[r].y);
+                sz[used + lane] = __float_as_uint(q[r].z);
+            }
+            for (int c = 64 + lane; c < len[r]; c += 64) {
+                const float4 v = spts[s0[r] + c];
+                sx[used + c] = __float_as_uint(v.x);
+                sy[used + c] = __float_as_uint(v.y);
+                sz[used + c] = __float_as_uint(v.z);
+            }
+            if (mine) {
+                if (r == 0) self = (int)(t - s0[0]) + used;
+                if (e0[r] < e1[r])
+                    ranges[nr++][lane] = (e0[r] - s0[r] + used) | ((e1[r] - s0[r] + used) << 16);
+            }
+            used += len[r];
+        }
+    }
+    __syncthreads();
+    if (active) {
         float best[K];
 #pragma unroll
         for (int u = 0; u < K; ++u) best[u] = __builtin_huge_valf();
         int found = 0;
-        auto scan = [&](unsigned e0, unsigned e1) {
-            // candidates eight at a time: the eight loads are in flight together
-            for (unsigned e = e0; e < e1; e += 8) {
-                float4 q[8];
+        // one candidate; best[] stays sorted ascending, one median per kept value
+        auto take = [&](float x, float y, float z, bool other) {
+            const float ex = x - px, ey = y - py, ez = z - pz;
+            const float sd = (ex * ex + ey * ey) + ez * ez;
+            const bool ok = sd <= rr && other;
+            found += ok;
+            const float v = ok ? sd : __builtin_huge_valf();
 #pragma unroll
-                for (int u = 0; u < 8; ++u) q[u] = spts[min(e + u, e1 - 1)];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    if (e + u >= e1 || __float_as_int(q[u].w) == i) continue;
-                    const float ex = q[u].x - px, ey = q[u].y - py, ez = q[u].z - pz;
-                    float sd = (ex * ex + ey * ey) + ez * ez;
-                    if (!(sd <= rr)) continue;
-                    ++found;
-                    // no smaller than the largest kept value: best[] would not change
-                    if (sd >= best[K - 1]) continue;
-                    // one compare-exchange pass keeps best[] sorted ascending
-#pragma unroll
-                    for (int u2 = 0; u2 < K; ++u2) {
-                        const float lo = fminf(best[u2], sd), hi = fmaxf(best[u2], sd);
-                        best[u2] = lo;
-                        sd = hi;
-                    }
+            for (int u = K - 1; u > 0; --u) best[u] = __builtin_amdgcn_fmed3f(best[u - 1], best[u], v);
+            best[0] = fminf(best[0], v);
+        };
+        int ng = 0;   // ranges of spts left to read from memory, in buf
+        auto later = [&](unsigned g0, unsigned g1) {
+            if (g0 < g1) {
+                buf[(2 * ng) * 64 + lane] = g0;
+                buf[(2 * ng + 1) * 64 + lane] = g1;
+                ++ng;
+            }
+        };
+        if (fits) {
+            // a slot past its range's end reads the point itself, which is no
+            // candidate
+            constexpr int S = 4;
+            int ri = 0, cur = 0, end = 0;
+            int at[S];
+            float qx[S], qy[S], qz[S];
+            auto fetch = [&]() -> bool {
+                if (cur >= end) {
+                    if (ri >= nr) return false;
+                    const uint32_t g = ranges[ri++][lane];
+                    cur = (int)(g & 0xFFFFu);
+                    end = (int)(g >> 16);
                 }
-            }
-        };
-        // the cells x0..x1 (offsets from cx, x0 <= x1) of one row: one range,
-        // or two where the run wraps round the table
-        auto scan_cells = [&](unsigned row, int x0, int x1) {
-            const unsigned xs = (unsigned)(cx + x0) & w.mx, xe = (unsigned)(cx + x1) & w.mx;
-            const bool wraps = xs > xe;
-            const unsigned ea = wraps ? w.mx : xe;
-            unsigned r0 = start[row | xs], r1 = start[row | ea] + count[row | ea];
-            unsigned s0 = wraps ? start[row] : 0u, s1 = wraps ? start[row | xe] + count[row | xe] : 0u;
-#pragma unroll 1
-            for (int part = 0; part < 2; ++part) {
-                scan(r0, r1);
-                r0 = s0;
-                r1 = s1;
-            }
-        };
-        // distance from the point to the box of the cell at offset o along one
-        // axis (0 for its own cell), less the slack
-        auto gap = [&](int o, int cc, float pp) {
-            const float lo = (float)(cc + o) * h, hi = (float)(cc + o + 1) * h;
-            const float gg = o < 0 ? pp - hi : (o > 0 ? lo - pp : 0.0f);
-            return fmaxf(gg - slack, 0.0f);
-        };
-        auto kth = [&]() {
-            float v = __builtin_huge_valf();
 #pragma unroll
-            for (int u = 0; u < K; ++u)
-                if (u == k - 1) v = best[u];
-            return found >= k ? v : __builtin_huge_valf();
-        };
-        // the own cell
-        scan_cells(bucket(0, cy, cz, w), 0, 0);
-        // the 25 runs, nearest first: (dy, dz) by |dy| + |dz|, then max
-        constexpr int RY[25] = {0, -1, 1, 0, 0, -1, 1, -1, 1, -2, 2, 0, 0, -2, 2, -2, 2, -1, 1, -1, 1, -2, 2, -2, 2};
-        constexpr int RZ[25] = {0, 0, 0, -1, 1, -1, -1, 1, 1, 0, 0, -2, 2, -1, -1, 1, 1, -2, -2, 2, 2, -2, -2, 2, 2};
+                for (int u = 0; u < S; ++u) {
+                    at[u] = cur + u < end ? cur + u : self;
+                    qx[u] = __uint_as_float(sx[at[u]]);
+                    qy[u] = __uint_as_float(sy[at[u]]);
+                    qz[u] = __uint_as_float(sz[at[u]]);
+                }
+                cur += S;
+                return true;
+            };
+            bool more = fetch();
+            while (more) {
+                float x[S], y[S], z[S];
+                bool other[S];
+#pragma unroll
+                for (int u = 0; u < S; ++u) {
+                    x[u] = qx[u];
+                    y[u] = qy[u];
+                    z[u] = qz[u];
+                    other[u] = at[u] != self;
+                }
+                more = fetch();
+#pragma unroll
+                for (int u = 0; u < S; ++u) take(x[u], y[u], z[u], other[u]);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 9; ++r) later(e0[r], e1[r]);
+        }
+        // from here on a lane overwrites candidates: every lane is past its own
+        __builtin_amdgcn_wave_barrier();
+        if (xw == 0 || xw == w.mx) {   // the cell on the other side of the table
+            uint2 c[9];
+#pragma unroll
+            for (int r = 0; r < 9; ++r) c[r] = table[bucket(0, cy + RY[r], cz + RZ[r], w) | (xw == 0 ? w.mx : 0u)];
+#pragma unroll
+            for (int r = 0; r < 9; ++r) later(c[r].x, c[r].x + c[r].y);
+        }
 #pragma unroll 1
-        for (int r = 0; r < 25; ++r) {
-            const int oy = RY[r], oz = RZ[r];
-            const float gy = gap(oy, cy, py), gz = gap(oz, cz, pz);
-            const float base = gy * gy + gz * gz;
-            const float kb = kth();
-            if (base > kb) continue;
-            // the x offsets still within reach: gaps grow with |dx|
-            int x0 = -2, x1 = 2;
-            while (x0 < 0) {
-                const float g = gap(x0, cx, px);
-                if (base + g * g <= kb) break;
-                ++x0;
-            }
-            while (x1 > 0) {
-                const float g = gap(x1, cx, px);
-                if (base + g * g <= kb) break;
-                --x1;
-            }
-            const unsigned row = bucket(0, cy + oy, cz + oz, w);
-            if (r == 0) {   // the own run without the own cell
-                if (x0 < 0) scan_cells(row, x0, -1);
-                if (x1 > 0) scan_cells(row, 1, x1);
-            } else {
-                scan_cells(row, x0, x1);
+        for (int g = 0; g < ng; ++g) {
+            const unsigned g0 = buf[(2 * g) * 64 + lane], g1 = buf[(2 * g + 1) * 64 + lane];
+#pragma unroll 1
+            for (unsigned e = g0; e < g1; e += 4) {
+                float4 q[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) q[u] = spts[min(e + u, g1 - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) take(q[u].x, q[u].y, q[u].z, e + u < g1 && __float_as_int(q[u].w) != i);
             }
         }
         const int m = min(found, k);
@@ -344,16 +439,20 @@ __global__ __launch_bounds__(256) void k_sor_knn(int k, float R, float h, Wrap w
     a2 = wave_sum(a2);
     a3 = wave_sum(a3);
     if ((threadIdx.x & 63) == 0 && a3) {
-        atomicAdd(acc + 0, a1);
-        atomicAdd(acc + 1, a2);
-        atomicAdd(acc + 2, a3);
+        unsigned long long* a = acc + (blockIdx.x % ACC_SLOTS) * ACC_LINE;
+        atomicAdd(a + 0, a1);
+        atomicAdd(a + 1, a2);
+        atomicAdd(a + 2, a3);
     }
 }
 
+// By whole waves: lane l adds up slot l.
 __device__ __forceinline__ double sor_threshold(const unsigned long long* acc, double alpha,
                                                 double* mu_out, double* sigma_out)
 {
-    const long long S1 = (long long)acc[0], S2 = (long long)acc[1], cnt = (long long)acc[2];
+    static_assert(ACC_SLOTS == 64, "one slot per lane");
+    const unsigned long long* a = acc + (threadIdx.x & 63) * ACC_LINE;
+    const long long S1 = (long long)wave_sum(a[0]), S2 = (long long)wave_sum(a[1]), cnt = (long long)wave_sum(a[2]);
     double mu = 0.0, sigma = 0.0;
     if (cnt > 0) mu = (double)S1 / SCALE1 / (double)cnt;
     if (cnt > 1) {
@@ -428,39 +527,31 @@ int edt_outlier_filter(const float* pts, int64_t n, int32_t k, float radius, flo
     const SorLayout L = sor_layout(n);
     char* w = static_cast<char*>(ws);
     unsigned* count = reinterpret_cast<unsigned*>(w + L.count);
-    unsigned* start = reinterpret_cast<unsigned*>(w + L.start);
-    unsigned* cursor = reinterpret_cast<unsigned*>(w + L.cursor);
-    unsigned* sums = reinterpret_cast<unsigned*>(w + L.sums);
+    uint2* table = reinterpret_cast<uint2*>(w + L.table);
     float4* spts = reinterpret_cast<float4*>(w + L.spts);
     unsigned long long* acc = reinterpret_cast<unsigned long long*>(w + L.acc);
     float* dm = mean_dist ? mean_dist : reinterpret_cast<float*>(w + L.total);
     const int T = (int)L.tmask + 1;
-    const float h = radius * 0.5005f;
+    const float h = radius * 1.001f;
     const hipStream_t st = as_stream(stream);
     const unsigned pblocks = (unsigned)((std::max<int64_t>(n, 1) + 255) / 256);
-    hipLaunchKernelGGL(k_sor_zero, dim3((T + 255) / 256), dim3(256), 0, st, count, cursor, T, acc);
+    hipLaunchKernelGGL(k_sor_zero, dim3((std::max(T / 4, ACC_GIVEN + 1) + 255) / 256), dim3(256), 0, st, reinterpret_cast<uint4*>(count), T / 4, acc);
     int rc = check_launch("k_sor_zero");
     if (rc) return rc;
     if (n > 0) {
         hipLaunchKernelGGL(k_sor_count, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, count, dm);
         if ((rc = check_launch("k_sor_count"))) return rc;
-    }
-    hipLaunchKernelGGL(k_scan_blocks, dim3(L.nsums), dim3(256), 0, st, count, start, sums);
-    if ((rc = check_launch("k_scan_blocks"))) return rc;
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, sums, L.nsums);
-    if ((rc = check_launch("k_scan_sums"))) return rc;
-    hipLaunchKernelGGL(k_scan_add, dim3(L.nsums), dim3(256), 0, st, start, sums);
-    if ((rc = check_launch("k_scan_add"))) return rc;
-    if (n > 0) {
-        hipLaunchKernelGGL(k_sor_scatter, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, start,
-                           cursor, spts);
+        hipLaunchKernelGGL(k_sor_place, dim3((T / 4 + 256 * PLACE_PER - 1) / (256 * PLACE_PER)), dim3(256), 0, st,
+                           reinterpret_cast<const uint4*>(count), T / 4, reinterpret_cast<uint4*>(table), acc);
+        if ((rc = check_launch("k_sor_place"))) return rc;
+        hipLaunchKernelGGL(k_sor_scatter, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, table, count, spts);
         if ((rc = check_launch("k_sor_scatter"))) return rc;
         if (k <= 8)
-            hipLaunchKernelGGL(k_sor_knn<8>, dim3(pblocks), dim3(256), 0, st, (int)k, radius, h, L.wrap,
-                               (unsigned)T, start, count, spts, dm, acc);
+            hipLaunchKernelGGL(k_sor_knn<8>, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, (int)k, radius, h, L.wrap, table, spts,
+                               dm, acc);
         else
-            hipLaunchKernelGGL(k_sor_knn<KMAX>, dim3(pblocks), dim3(256), 0, st, (int)k, radius, h, L.wrap,
-                               (unsigned)T, start, count, spts, dm, acc);
+            hipLaunchKernelGGL(k_sor_knn<KMAX>, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, (int)k, radius, h, L.wrap, table,
+                               spts, dm, acc);
         if ((rc = check_launch("k_sor_knn"))) return rc;
     }
     hipLaunchKernelGGL(k_sor_keep, dim3(pblocks), dim3(256), 0, st, pts, n, dm, acc, (double)alpha,
