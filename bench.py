@@ -49,7 +49,7 @@ XY_BYTES_PER_VOXEL = 1 + 4      # occupancy byte in, packed 2D site out
 Z_BYTES_PER_VOXEL = 4 + 8       # packed 2D site in, d2 + site out
 EDT_BYTES_PER_VOXEL = 9         # compulsory: occupancy in, d2 + site out
 # the kernels of each pass on the control-cycle map (the search tiles)
-XY_KERNELS = ["k_row_records", "k_edt_xy_search"]
+XY_KERNELS = ["k_map_bits", "k_edt_xy_search"]
 Z_KERNELS = ["k_edt_z_search"]
 
 
