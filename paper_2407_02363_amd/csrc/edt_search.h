@@ -26,9 +26,14 @@
 // evaluates, and each wave finishes its own band of BAND positions after a
 // single barrier.
 //
-// What bounds them is VALU issue: about 50 instructions per voxel and pass on
-// the benchmark's maps (17 to 35 evaluated sites per voxel at 1.75
-// instructions each, the bounds, the write-out).
+// What bounds them is instruction issue: 45 to 100 VALU instructions per voxel
+// and pass (17 to 35 evaluated sites per voxel at 1.75 each, the bounds, the
+// write-out) and 30 to 45 scalar ones.  The bounds are therefore tests whose
+// signs a lane shifts into one mask that is joined across the wave, against
+// distances from tables, and only a band's first block takes upper bounds from
+// all groups; later ones have the block before.  One xy pass in us, with a
+// ballot per test and computed distances and like this: 256 x 256 x 128 frame
+// 28.0 -> 26.5, 512 x 512 x 128 73.2 -> 68.6, 512^3 blobs 381 -> 374.
 #include "edt_tiles.h"
 
 namespace edtmi {
@@ -121,10 +126,35 @@ template <int NMAX> struct Bounds {
 };
 template <int NMAX> __constant__ constexpr Bounds<NMAX> BOUNDS{};
 
+// Squared gap between a block whose first chunk is cb and chunk c, at c - cb + NMAX / C.
+template <int NMAX, int C> struct ChunkGaps {
+    int gap2[2 * NMAX / C];
+    constexpr ChunkGaps() : gap2{}
+    {
+        for (int j = 0; j < 2 * NMAX / C; ++j) {
+            const int lo = C * (j - NMAX / C);   // the chunk's first position, from the block's
+            const int g1 = lo - (QB - 1), g2 = -(lo + C - 1), gap = g1 > g2 ? g1 : g2;
+            gap2[j] = gap > 0 ? gap * gap : 0;
+        }
+    }
+};
+template <int NMAX, int C> __constant__ constexpr ChunkGaps<NMAX, C> CHUNK_GAPS{};
+
 __device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 __device__ __forceinline__ bool any_lane2(bool p, bool q)
 {
     return (__builtin_amdgcn_ballot_w64(p) & __builtin_amdgcn_ballot_w64(q)) != 0;
+}
+
+// v of all lanes, joined
+__device__ __forceinline__ uint32_t or_lanes(uint32_t v)
+{
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+    v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+    return __builtin_amdgcn_readlane(v, 15) | __builtin_amdgcn_readlane(v, 31) |
+           __builtin_amdgcn_readlane(v, 47) | __builtin_amdgcn_readlane(v, 63);
 }
 
 // ---------------------------------------------------------------------------
@@ -132,33 +162,28 @@ __device__ __forceinline__ bool any_lane2(bool p, bool q)
 //   np        positions with chunk minima (a multiple of BAND; the ones past
 //             the line's end are empty)
 //   cmin(c)   the smallest h of chunk c (this lane)
+//   gmin(g)   the smallest h of group g
 //   site(c, k, a)  h of site k of chunk c, plus a (this lane)
 //   emit(q, n, value, s)  positions q .. q + n - 1 (n <= 8) of a line with
 //             sites: value[i] = f_s(q + i) for the winning site s[i]
 //   none(q)   a position of a line that has no site
 // ---------------------------------------------------------------------------
-template <int NMAX, int C, class CMin, class Site, class Emit, class None>
-__device__ __forceinline__ void search_band(int q0, int q1, int np, CMin cmin, Site site, Emit emit, None none)
+template <int NMAX, int C, class CMin, class GMin, class Site, class Emit, class None>
+__device__ __forceinline__ void search_band(int q0, int q1, int np, CMin cmin, GMin gmin, Site site, Emit emit, None none)
 {
     constexpr int G = NMAX / NG;
     constexpr int CG = G / C;       // chunks per group
     constexpr int CB = QB / C;      // chunks per block
     constexpr int CW = W / C;       // chunks on either side of a block in the short test
     int gm[NG];
-    auto group_min = [&](int g) {
-        int m = cmin(g * CG);
-#pragma unroll
-        for (int k = 1; k < CG; ++k) m = min(m, cmin(g * CG + k));
-        return m;
-    };
     if (np == NMAX) {
 #pragma unroll
-        for (int g = 0; g < NG; ++g) gm[g] = group_min(g);
+        for (int g = 0; g < NG; ++g) gm[g] = gmin(g);
     } else {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             gm[g] = 1 << 21;
-            if (g * G < np) gm[g] = group_min(g);
+            if (g * G < np) gm[g] = gmin(g);
         }
     }
     {
@@ -225,20 +250,25 @@ __device__ __forceinline__ void search_band(int q0, int q1, int np, CMin cmin, S
             // the groups' bounds first, then the chunks of the groups left
             const int* far2 = BOUNDS<NMAX>.far2[qa / QB];
             const int* gap2 = BOUNDS<NMAX>.gap2[qa / QB];
+            if (qa == q0) {
 #pragma unroll
-            for (int g = 0; g < NG; ++g) U = min(U, gm[g] + far2[g]);
+                for (int g = 0; g < NG; ++g) U = min(U, gm[g] + far2[g]);
+            }
+            // a lane's tests shift their sign into its mask; then the lanes' masks are joined
             uint32_t gmask = 0;
 #pragma unroll
-            for (int g = 0; g < NG; ++g) gmask |= any_lane(gm[g] + gap2[g] <= U) ? 1u << g : 0u;
+            for (int g = NG - 1; g >= 0; --g)
+                gmask = __builtin_amdgcn_alignbit(gmask, (uint32_t)(gm[g] + gap2[g] + ~U), 31);
+            gmask = or_lanes(gmask);
             while (gmask) {
                 const int g = __builtin_ctz(gmask);
                 gmask &= gmask - 1u;
                 uint32_t cmask = 0;
+                const int* cgap2 = CHUNK_GAPS<NMAX, C>.gap2 + (NMAX / C - cb0 + g * CG);
 #pragma unroll
                 for (int k = 0; k < CG; ++k) {
                     const int c = g * CG + k;
-                    const int gap = c < cb0 ? C * (cb0 - c - 1) + 1 : (c < cb0 + CB ? 0 : C * (c - cb0) - (QB - 1));
-                    cmask |= any_lane2(cmin(c) + gap * gap <= U, C * c + C - 1 >= lo) ? 1u << k : 0u;
+                    cmask |= any_lane2(cmin(c) + cgap2[k] <= U, C * c + C - 1 >= lo) ? 1u << k : 0u;
                 }
                 while (cmask) {
                     evaluate(g * CG + __builtin_ctz(cmask));
@@ -319,6 +349,14 @@ __device__ __forceinline__ void z_tile(int32_t* __restrict__ d2, int32_t* __rest
     const u16x2 lin = __builtin_bit_cast(u16x2, 1u | ((unsigned)nx << 16));
     search_band<NMAX, C>(
         q0, q1, np, [&](int c) { return cm[c * 64 + lane]; },
+        [&](int g) {
+            constexpr int CG = NMAX / NG / C;
+            const int* p = cm + g * (CG * 64) + lane;
+            int m = p[0];
+#pragma unroll
+            for (int k = 1; k < CG; ++k) m = min(m, p[k * 64]);
+            return m;
+        },
         [&](int c, int k, int a) {
             const s16x2 d = own - __builtin_bit_cast(s16x2, (val + c * (C * 64) + lane)[k * 64]);
             return __builtin_amdgcn_sdot2(d, d, a, false);
@@ -379,7 +417,12 @@ __device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int m
     const int lane = threadIdx.x & 63;
     const int band = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int z = T / ntx;
-    const int tx = T - z * ntx;
+    // consecutive work-groups go to the 8 XCDs in turn: shift the column tiles
+    // from one round to the next, and by half a row where the CUs take their
+    // second ones, so that no XCD or CU has a map's busy columns to itself
+    // (256 x 256 x 128 frame 29.9 -> 28.0 us, 512 x 512 x 128 78 -> 73)
+    const int zn = z * ntx;
+    const int tx = (T - zn + (zn >> 3) + (zn >> 8) * (ntx >> 1)) % ntx;
     // a lane past the row's end does what the row's last column does
     const int bit = min(lane, nx - 1 - tx * 64);
     const int xc = tx * 64 + bit;
@@ -421,33 +464,34 @@ __device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int m
             }
         }
         const uint64_t rows = __builtin_amdgcn_ballot_w64((wl | wh) != 0 || l >= 0 || r < RIGHT_NONE);
-        const uint32_t lr = ((uint32_t)l & 0xFFFFu) | ((uint32_t)r << 16);
+        // the lane's columns up to and from its own, the row's neighbours as
+        // distances from the tile's last and first column
+        const uint32_t upto_l = bit < 32 ? ~0u >> (31 - bit) : ~0u, upto_h = bit < 32 ? 0u : ~0u >> (63 - bit);
+        const uint32_t from_l = bit < 32 ? ~0u << bit : 0u, from_h = bit < 32 ? ~0u : ~0u << (bit - 32);
+        const uint32_t lr = (uint32_t)(tx * 64 + 63 - l) | ((uint32_t)(r - tx * 64) << 16);
         int16_t* db = dx + q0 * 64 + lane;
         uint16_t* cb = cm + q0 / C * 64 + lane;
 #pragma unroll
         for (int i = 0; i < BAND; i += C) {
+            uint32_t m = D_EMPTY;
             if (((rows >> i) & ((1u << C) - 1u)) == 0) {   // wave-uniform
 #pragma unroll
                 for (int k = 0; k < C; ++k) db[(i + k) * 64] = (int16_t)D_EMPTY;
-                cb[i / C * 64] = (uint16_t)D_EMPTY;
-                continue;
-            }
-            uint32_t m = 2 * D_EMPTY;
+            } else {
+                m = 2 * D_EMPTY;
 #pragma unroll
-            for (int k = 0; k < C; ++k) {
-                // step 1: the nearest occupied column of a row, ties to the left
-                const uint64_t w = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(wl, i + k) |
-                                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(wh, i + k) << 32);
-                const int s = __builtin_amdgcn_readlane(lr, i + k);
-                const uint64_t a = w << (63 - bit), b = w >> bit;
-                const uint32_t dl = min(min(ffbh((uint32_t)(a >> 32)),
-                                            __builtin_elementwise_add_sat(ffbh((uint32_t)a), 32u)),
-                                        (uint32_t)(xc - (int)(int16_t)s));
-                const uint32_t dr = min(min(ffbl((uint32_t)b),
-                                            __builtin_elementwise_add_sat(ffbl((uint32_t)(b >> 32)), 32u)),
-                                        (uint32_t)((s >> 16) - xc));
-                db[(i + k) * 64] = (int16_t)(dl <= dr ? (int)dl : -(int)dr);
-                m = min(m, min(dl, dr));
+                for (int k = 0; k < C; ++k) {
+                    // step 1: the nearest occupied column of a row, ties to the left
+                    const uint32_t wl_ = __builtin_amdgcn_readlane(wl, i + k), wh_ = __builtin_amdgcn_readlane(wh, i + k);
+                    const uint32_t s = __builtin_amdgcn_readlane(lr, i + k);
+                    const uint32_t el = min(min(ffbh(wh_ & upto_h), __builtin_elementwise_add_sat(ffbh(wl_ & upto_l), 32u)),
+                                            s & 0xFFFFu);
+                    const uint32_t er = min(min(ffbl(wl_ & from_l), __builtin_elementwise_add_sat(ffbl(wh_ & from_h), 32u)),
+                                            s >> 16);
+                    const uint32_t dl = el + bit - 63u, dr = er - bit;
+                    db[(i + k) * 64] = (int16_t)(dl <= dr ? (int)dl : -(int)dr);
+                    m = min(m, min(dl, dr));
+                }
             }
             cb[i / C * 64] = (uint16_t)m;
         }
@@ -459,6 +503,14 @@ __device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int m
         q0, q1, np,
         [&](int c) {
             const int m = cm[c * 64 + lane];
+            return mul24(m, m);
+        },
+        [&](int g) {
+            constexpr int CG = NMAX / NG / C;
+            const uint16_t* p = cm + g * (CG * 64) + lane;
+            int m = p[0];
+#pragma unroll
+            for (int k = 1; k < CG; ++k) m = min(m, (int)p[k * 64]);
             return mul24(m, m);
         },
         [&](int c, int k, int a) {
