@@ -116,8 +116,12 @@ template <int NMAX, int C, int BAND, class Set>
 __global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_xy_search(Set s, int waves)
 {
     extern __shared__ uint32_t lds[];
-    // as in k_edt_xy: chunks of 16 tiles per XCD, rotating over the XCDs
-    const int T = xcd_chunk_remap(blockIdx.x, gridDim.x, 16);
+    // tiles in launch order: a tile reads 1 bit per voxel and writes whole
+    // cache lines, so neighbours share next to nothing, and chunks of tiles per
+    // XCD leave some XCDs more of the busy slices than others (xy pass of a
+    // 512 x 512 x 128 frame 69 us in chunks of 16, 64 like this; 48 self maps
+    // 452 against 440 in all)
+    const int T = (int)blockIdx.x;
     const EdtMap& d = tile_map(s, T);
     if (gated_off(d)) return;
     search::xy_tile<NMAX, C, BAND>(reinterpret_cast<const uint32_t*>(d.d2), search::misalignment(d.occ),

@@ -417,12 +417,11 @@ __device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int m
     const int lane = threadIdx.x & 63;
     const int band = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int z = T / ntx;
-    // consecutive work-groups go to the 8 XCDs in turn: shift the column tiles
-    // from one round to the next, and by half a row where the CUs take their
-    // second ones, so that no XCD or CU has a map's busy columns to itself
-    // (256 x 256 x 128 frame 29.9 -> 28.0 us, 512 x 512 x 128 78 -> 73)
+    // the CUs take their second work-groups 256 tiles after their first ones:
+    // shift the column tiles by half a row from there on, or a CU gets a map's
+    // busy columns twice (256 x 256 x 128 frame 29.9 -> 28.0 us)
     const int zn = z * ntx;
-    const int tx = (T - zn + (zn >> 3) + (zn >> 8) * (ntx >> 1)) % ntx;
+    const int tx = (T - zn + (zn >> 8) * (ntx >> 1)) % ntx;
     // a lane past the row's end does what the row's last column does
     const int bit = min(lane, nx - 1 - tx * 64);
     const int xc = tx * 64 + bit;
