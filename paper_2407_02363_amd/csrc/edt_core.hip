@@ -103,24 +103,61 @@ __global__ __launch_bounds__(256) void k_map_bits(Set s)
 }
 
 template <int NMAX, int C, int BAND, class Set>
-__global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_z_search(Set s, int waves)
+__global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_z_search(Set s, int waves, int)
 {
     extern __shared__ uint32_t lds[];
     const int T = (int)blockIdx.x;
     const EdtMap& d = tile_map(s, T);
     if (gated_off(d)) return;
-    search::z_tile<NMAX, C, BAND>(d.d2, d.site, d.nx, d.ny, d.nz, T - d.begin, BAND * waves, lds);
+    search::ZBand<BAND> b;
+    b.load(d.d2, d.site, d.nx, d.ny, d.nz, T - d.begin, search::band_of_wave() * BAND);
+    search::z_stage<C>(b, BAND * waves, lds);
+    __syncthreads();
+    search::z_band<NMAX, C, BAND>(b, BAND * waves, lds);
+}
+
+// The same for lines of more than 256 positions, whose tile takes most of a
+// CU's local memory: one work-group per CU walks over the tiles, and the sites
+// of its next tile are on their way while it searches the present one, which a
+// second resident work-group does for shorter lines.  A tile reads and writes
+// its own columns only, so the loads of one may pass the stores of another.
+// z pass of 512^3 blobs 457 -> 420 us, of a 256 x 256 x 512 frame 117 -> 113; 265 us
+// of the 420 are VALU issue, the rest is mostly waiting for a tile's slowest band.
+template <int NMAX, int C, int BAND, class Set>
+__global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_z_stream(Set s, int waves, int total)
+{
+    extern __shared__ uint32_t lds[];
+    const int q0 = search::band_of_wave() * BAND, np = BAND * waves;
+    search::ZBand<BAND> next;
+    auto fetch = [&](int T) -> bool {   // the same for the whole work-group
+        const EdtMap& d = tile_map(s, T);
+        if (gated_off(d)) return false;
+        next.load(d.d2, d.site, d.nx, d.ny, d.nz, T - d.begin, q0);
+        return true;
+    };
+    int T = (int)blockIdx.x;
+    bool on = fetch(T);
+    for (;;) {
+        const search::ZTile tile = next;
+        if (on) search::z_stage<C>(next, np, lds);
+        __syncthreads();
+        const bool now = on;
+        T += (int)gridDim.x;
+        on = T < total && fetch(T);
+        if (now) search::z_band<NMAX, C, BAND>(tile, np, lds);
+        if (T >= total) return;
+        __syncthreads();
+    }
 }
 
 template <int NMAX, int C, int BAND, class Set>
-__global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_xy_search(Set s, int waves)
+__global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_xy_search(Set s, int waves, int)
 {
     extern __shared__ uint32_t lds[];
     // tiles in launch order: a tile reads 1 bit per voxel and writes whole
     // cache lines, so neighbours share next to nothing, and chunks of tiles per
-    // XCD leave some XCDs more of the busy slices than others (xy pass of a
-    // 512 x 512 x 128 frame 69 us in chunks of 16, 64 like this; 48 self maps
-    // 452 against 440 in all)
+    // XCD leave some XCDs more of the busy slices than others (48 self maps 449
+    // us in chunks of 16, 438 like this; single maps within 3% either way)
     const int T = (int)blockIdx.x;
     const EdtMap& d = tile_map(s, T);
     if (gated_off(d)) return;
@@ -198,6 +235,17 @@ int launch_map_bits(const EdtMapSet& s, hipStream_t st)
     return check_launch("k_map_bits");
 }
 
+// CUs of the current device, 0 on an error.
+int cu_count()
+{
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+        return n;
+    set_error("the device's CU count could not be read");
+    return 0;
+}
+
 // One pass of the search tiles; n = the longest line of the pass.
 template <int NMAX, int BAND>
 int launch_search_t(const EdtMapSet& s, bool z_pass, int n, hipStream_t st)
@@ -208,21 +256,30 @@ int launch_search_t(const EdtMapSet& s, bool z_pass, int n, hipStream_t st)
     // (512 x 512 x 128 frame 84 against 93 us, 512^3 blobs 431 against 436)
     constexpr int C = NMAX <= 256 ? 4 : 8;
     const int nw = (n + BAND - 1) / BAND, np = nw * BAND;
-    auto go = [&](auto kernel, bool& done, size_t lds, const auto& arg, const char* name) -> int {
+    auto go = [&](auto kernel, bool& done, size_t lds, const auto& arg, const char* name, int grid) -> int {
         int rc = allow_lds(kernel, done);
         if (rc) return rc;
-        hipLaunchKernelGGL(kernel, dim3(s.total), dim3(64 * nw), lds, st, arg, nw);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * nw), lds, st, arg, nw, s.total);
         return check_launch(name);
     };
     static bool done[4];
     if (z_pass) {
         const size_t lds = (size_t)(np + np / C) * 256;
-        return s.n == 1 ? go(k_edt_z_search<NMAX, C, BAND, EdtMap>, done[0], lds, s.m[0], "k_edt_z_search")
-                        : go(k_edt_z_search<NMAX, C, BAND, EdtMapSet>, done[1], lds, s, "k_edt_z_search");
+        if constexpr (NMAX > 256) {
+            const int n_cu = cu_count();
+            if (!n_cu) return EDT_ERR_HIP;
+            const int grid = std::min(s.total, n_cu);
+            return s.n == 1 ? go(k_edt_z_stream<NMAX, C, BAND, EdtMap>, done[0], lds, s.m[0], "k_edt_z_stream", grid)
+                            : go(k_edt_z_stream<NMAX, C, BAND, EdtMapSet>, done[1], lds, s, "k_edt_z_stream", grid);
+        } else {
+            return s.n == 1
+                       ? go(k_edt_z_search<NMAX, C, BAND, EdtMap>, done[0], lds, s.m[0], "k_edt_z_search", s.total)
+                       : go(k_edt_z_search<NMAX, C, BAND, EdtMapSet>, done[1], lds, s, "k_edt_z_search", s.total);
+        }
     }
     const size_t lds = (size_t)(np + np / C) * 128;
-    return s.n == 1 ? go(k_edt_xy_search<NMAX, C, BAND, EdtMap>, done[2], lds, s.m[0], "k_edt_xy_search")
-                    : go(k_edt_xy_search<NMAX, C, BAND, EdtMapSet>, done[3], lds, s, "k_edt_xy_search");
+    return s.n == 1 ? go(k_edt_xy_search<NMAX, C, BAND, EdtMap>, done[2], lds, s.m[0], "k_edt_xy_search", s.total)
+                    : go(k_edt_xy_search<NMAX, C, BAND, EdtMapSet>, done[3], lds, s, "k_edt_xy_search", s.total);
 }
 
 int launch_search(const EdtMapSet& s, bool z_pass, hipStream_t st)

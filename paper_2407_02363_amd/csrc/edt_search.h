@@ -140,6 +140,7 @@ template <int NMAX, int C> struct ChunkGaps {
 };
 template <int NMAX, int C> __constant__ constexpr ChunkGaps<NMAX, C> CHUNK_GAPS{};
 
+__device__ __forceinline__ int band_of_wave() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
 __device__ __forceinline__ bool any_lane(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 __device__ __forceinline__ bool any_lane2(bool p, bool q)
 {
@@ -301,50 +302,82 @@ __device__ __forceinline__ void search_band(int q0, int q1, int np, CMin cmin, G
 //   lds   np * 256 bytes of sites [slice][lane], then np / C * 256 bytes of
 //         chunk minima, np = BAND * waves >= nz
 // ---------------------------------------------------------------------------
-template <int NMAX, int C, int BAND>
-__device__ __forceinline__ void z_tile(int32_t* __restrict__ d2, int32_t* __restrict__ site, int nx, int ny,
-                                       int nz, int T, int np, uint32_t* lds)
+// A wave's place in one column tile, and its band's sites on their way from
+// memory.
+struct ZTile {
+    int32_t *d2, *site;   // the tile's first column
+    unsigned plane, off;  // voxels per slice; the lane's column, clamped into the plane
+    int nx, nz;
+    s16x2 own;            // the lane's x and y
+    bool live;
+};
+template <int BAND> struct ZBand : ZTile {
+    uint32_t v[BAND];
+
+    __device__ __forceinline__ void load(int32_t* d2_, int32_t* site_, int nx_, int ny, int nz_, int T, int q0)
+    {
+        const int lane = threadIdx.x & 63;
+        nx = nx_;
+        nz = nz_;
+        plane = (unsigned)nx * (unsigned)ny;
+        const unsigned c0 = (unsigned)T * 64u;
+        const unsigned cc = min(c0 + lane, plane - 1u);
+        live = c0 + lane < plane;
+        off = cc - c0;
+        const unsigned y = cc / (unsigned)nx, x = cc - y * (unsigned)nx;
+        own = __builtin_bit_cast(s16x2, x | (y << 16));
+        d2 = d2_ + c0;
+        site = site_ + c0;
+        // all loads of the band in flight, clamped into the column
+        const uint32_t* in = reinterpret_cast<const uint32_t*>(site);
+#pragma unroll
+        for (int i = 0; i < BAND; ++i) v[i] = (in + (size_t)min(q0 + i, nz - 1) * plane)[off];
+    }
+};
+
+// the band's sites and chunk minima into local memory
+template <int C, int BAND>
+__device__ __forceinline__ void z_stage(ZBand<BAND>& b, int np, uint32_t* lds)
 {
     uint32_t* val = lds;
     int* cm = reinterpret_cast<int*>(lds + np * 64);
     const int lane = threadIdx.x & 63;
-    const int band = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const unsigned plane = (unsigned)nx * (unsigned)ny;
-    const unsigned c0 = (unsigned)T * 64u;
-    const unsigned cc = min(c0 + lane, plane - 1u);
-    const bool live = c0 + lane < plane;
-    const unsigned y = cc / (unsigned)nx, x = cc - y * (unsigned)nx;
-    const s16x2 own = __builtin_bit_cast(s16x2, x | (y << 16));
-    const int q0 = band * BAND;
-    const int q1 = min(nz, q0 + BAND);
-    const unsigned off = cc - c0;
-    {
-        // all loads of the band in flight, clamped into the column
-        uint32_t v[BAND];
-        const uint32_t* in = reinterpret_cast<const uint32_t*>(site) + c0;
+    const int q0 = band_of_wave() * BAND;
+    if (q0 + BAND > b.nz) {
 #pragma unroll
-        for (int i = 0; i < BAND; ++i) v[i] = (in + (size_t)min(q0 + i, nz - 1) * plane)[off];
-        if (q0 + BAND > nz) {
-#pragma unroll
-            for (int i = 0; i < BAND; ++i)
-                if (q0 + i >= nz) v[i] = XY_NONE;
-        }
-        uint32_t* vb = val + q0 * 64 + lane;
-        int* cb = cm + q0 / C * 64 + lane;
-#pragma unroll
-        for (int i = 0; i < BAND; i += C) {
-            int m = 1 << 21;
-#pragma unroll
-            for (int k = 0; k < C; ++k) {
-                const uint32_t e = v[i + k] == XY_NONE ? V_EMPTY : v[i + k];
-                vb[(i + k) * 64] = e;
-                const s16x2 d = own - __builtin_bit_cast(s16x2, e);
-                m = min(m, __builtin_amdgcn_sdot2(d, d, 0, false));
-            }
-            cb[i / C * 64] = m;
-        }
+        for (int i = 0; i < BAND; ++i)
+            if (q0 + i >= b.nz) b.v[i] = XY_NONE;
     }
-    __syncthreads();
+    uint32_t* vb = val + q0 * 64 + lane;
+    int* cb = cm + q0 / C * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < BAND; i += C) {
+        int m = 1 << 21;
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const uint32_t e = b.v[i + k] == XY_NONE ? V_EMPTY : b.v[i + k];
+            vb[(i + k) * 64] = e;
+            const s16x2 d = b.own - __builtin_bit_cast(s16x2, e);
+            m = min(m, __builtin_amdgcn_sdot2(d, d, 0, false));
+        }
+        cb[i / C * 64] = m;
+    }
+}
+
+// the band's results
+template <int NMAX, int C, int BAND>
+__device__ __forceinline__ void z_band(const ZTile& t, int np, uint32_t* lds)
+{
+    int32_t *__restrict__ d2 = t.d2, *__restrict__ site = t.site;
+    const unsigned plane = t.plane, off = t.off;
+    const int nx = t.nx, nz = t.nz;
+    const s16x2 own = t.own;
+    const bool live = t.live;
+    const uint32_t* val = lds;
+    const int* cm = reinterpret_cast<const int*>(lds + np * 64);
+    const int lane = threadIdx.x & 63;
+    const int q0 = band_of_wave() * BAND;
+    const int q1 = min(nz, q0 + BAND);
     if (q0 >= q1) return;
     const u16x2 lin = __builtin_bit_cast(u16x2, 1u | ((unsigned)nx << 16));
     search_band<NMAX, C>(
@@ -368,8 +401,8 @@ __device__ __forceinline__ void z_tile(int32_t* __restrict__ d2, int32_t* __rest
                 lx[i] = (int32_t)__builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, val[s[i] * 64 + lane]), lin,
                                                         __umul24(plane, (unsigned)s[i]), false);
             if (!live) return;
-            int32_t* od = d2 + c0 + (size_t)q * plane;
-            int32_t* os = site + c0 + (size_t)q * plane;
+            int32_t* od = d2 + (size_t)q * plane;
+            int32_t* os = site + (size_t)q * plane;
 #pragma unroll
             for (int i = 0; i < QB; ++i) {
                 if (i >= n) break;
@@ -381,8 +414,8 @@ __device__ __forceinline__ void z_tile(int32_t* __restrict__ d2, int32_t* __rest
         },
         [&](int q) {
             if (live) {
-                (d2 + c0 + (size_t)q * plane)[off] = 0x7FFFFFFF;
-                (site + c0 + (size_t)q * plane)[off] = -1;
+                (d2 + (size_t)q * plane)[off] = 0x7FFFFFFF;
+                (site + (size_t)q * plane)[off] = -1;
             }
         });
 }
@@ -415,7 +448,7 @@ __device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int m
     int16_t* dx = reinterpret_cast<int16_t*>(lds);
     uint16_t* cm = reinterpret_cast<uint16_t*>(dx + np * 64);
     const int lane = threadIdx.x & 63;
-    const int band = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int band = band_of_wave();
     const int z = T / ntx;
     // the CUs take their second work-groups 256 tiles after their first ones:
     // shift the column tiles by half a row from there on, or a CU gets a map's
