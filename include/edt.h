@@ -317,9 +317,9 @@ int edt_compute_tuned(const edt_grid_t* grid, const uint8_t* occ, int32_t* d2, i
  * callers that pipeline the passes of several maps.
  *   stage EDT_STAGE_XY: steps 1-3 of Sec. III-C in every z slice; writes the
  *         2D nearest site of each voxel, packed x' | y' << 16 (0xFFFFFFFF if
- *         the slice is empty), into site.  It may first write per-row
- *         records of step 1 into d2, as scratch; d2 holds nothing meaningful
- *         after this stage.
+ *         the slice is empty), into site.  It may first write the map's
+ *         occupancy bits or per-row records of step 1 into d2, as scratch; d2
+ *         holds nothing meaningful after this stage.
  *   stage EDT_STAGE_Z: step 4 (steps 2-3 along z); reads that packed form
  *         from site and overwrites d2 and site with the final result.
  *   stage EDT_STAGE_ALL: both, identical to edt_compute_tuned.
@@ -414,7 +414,7 @@ size_t edt_batch_workspace_bytes(int32_t n_maps);
  *   tuning  NULL = the batch autotuner's choice for this shape class, else
  *           xy_tile in {16, 32}, z_tile in {16, 32, 64} (z_group, xy_group ignored:
  *           batches use 256-thread work-groups), or xy_tile = z_tile = 64: the
- *           banded lean tiles of edt_compute (512-thread work-groups; every
+ *           banded lean tiles (512-thread work-groups; every
  *           axis at most 512, nz at least 1).
  * Errors: EDT_ERR_UNSUPPORTED for an axis above 512 or tiles that do not
  * fit; argument errors as for edt_compute.

@@ -1,7 +1,7 @@
 """The search tiles (every axis up to 512) at the sizes where they can go
 wrong, bit for bit against the oracle: the ends of blocks (8 positions),
 bands (8, 16, 32), groups and work-group sizes (64, 128, 256, 512 positions),
-tiles of 64 columns, rows too short for records; maps with one site, sites far
+tiles of 64 columns, maps too small for the bits; maps with one site, sites far
 apart (the bounds by groups), dense maps (the bounds by neighbours), no site.
 Integers throughout: nothing may differ.
 """
@@ -50,8 +50,8 @@ def test_search_tiles(shape, kind):
 
 @pytest.mark.parametrize("shift", [1, 2, 3])
 def test_outputs_off_16_bytes(shift):
-    """The row records start at d2's first 16-byte boundary and end inside it,
-    also for the shortest rows that hold them."""
+    """The occupancy bits stay inside d2, wherever it starts, also for the
+    smallest maps that hold them."""
     for shape in [(3, 5, 8), (20, 33, 70)]:
         occ = scene("half", shape, 3)
         n = occ.size
