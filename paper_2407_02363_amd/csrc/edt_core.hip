@@ -90,15 +90,16 @@ __global__ __launch_bounds__(NTZ) void k_edt_z(EdtMapSet s)
 __device__ __forceinline__ const EdtMap& tile_map(const EdtMap& m, int) { return m; }
 __device__ __forceinline__ const EdtMap& tile_map(const EdtMapSet& s, int T) { return s.m[map_of(s, T)]; }
 
-// Occupancy bits of every map, 256 words per work-group (d.begin: the map's
-// first work-group).
+// Occupancy bits of every map, 16 * 256 * BITS_U voxels per work-group
+// (d.begin: the map's first work-group).
 template <class Set>
 __global__ __launch_bounds__(256) void k_map_bits(Set s)
 {
     const int B = (int)blockIdx.x;
     const EdtMap& d = tile_map(s, B);
     if (gated_off(d)) return;
-    search::map_bits(d.occ, (int64_t)d.nx * d.ny * d.nz, (int64_t)(B - d.begin) * 256 + threadIdx.x,
+    search::map_bits(d.occ, (int64_t)d.nx * d.ny * d.nz,
+                     ((int64_t)(B - d.begin) * 4 + search::band_of_wave()) * (64 * search::BITS_U),
                      reinterpret_cast<uint32_t*>(d.d2));
 }
 
@@ -228,7 +229,7 @@ int launch_map_bits(const EdtMapSet& s, hipStream_t st)
     for (int i = 0; i < s.n; ++i) {
         const int64_t n = (int64_t)s.m[i].nx * s.m[i].ny * s.m[i].nz + search::misalignment(s.m[i].occ);
         r.m[i].begin = blocks;
-        blocks += (int)((n + 32 * 256 - 1) / (32 * 256));
+        blocks += (int)((n + 16 * 256 * search::BITS_U - 1) / (16 * 256 * search::BITS_U));
     }
     if (s.n == 1) hipLaunchKernelGGL(k_map_bits<EdtMap>, dim3(blocks), dim3(256), 0, st, r.m[0]);
     else hipLaunchKernelGGL(k_map_bits<EdtMapSet>, dim3(blocks), dim3(256), 0, st, r);

@@ -79,32 +79,63 @@ __device__ __forceinline__ uint32_t nonzero_high(uint32_t w)
     return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u;
 }
 
-// 32 voxels per thread: bytes [32 u, 32 u + 32) from the 16-byte boundary at
-// or below occ.  A word that sticks out of the map is read byte by byte, so no
+// 16 voxels as bits: bytes [16 c, 16 c + 16) from the 16-byte boundary at or
+// below occ.  A chunk that sticks out of the map is read byte by byte, so no
 // load leaves [occ, occ + n).
-__device__ __forceinline__ void map_bits(const uint8_t* __restrict__ occ, int64_t n, int64_t u,
+__device__ __forceinline__ uint32_t chunk_bits(const uint4& a)
+{
+    // the eight 0x80 flags of two words, weighted 1 .. 128: 128 times their bits
+    uint32_t t = __builtin_amdgcn_udot4(nonzero_high(a.x), 0x08040201u, 0u, false);
+    t = __builtin_amdgcn_udot4(nonzero_high(a.y), 0x80402010u, t, false);
+    uint32_t h = __builtin_amdgcn_udot4(nonzero_high(a.z), 0x08040201u, 0u, false);
+    h = __builtin_amdgcn_udot4(nonzero_high(a.w), 0x80402010u, h, false);
+    return (t >> 7) | (h >> 7) << 8;
+}
+
+// The words of one wave: BITS_U * 64 chunks from chunk c0 on, a load of the
+// wave covering 1 KiB in one piece, all loads in flight; an even lane joins its
+// chunk with its neighbour's to a word.  48 self maps of 128^3 32 us with two
+// loads in flight, 23 with four and 22 with eight (a work-group first finds its
+// map in the set); a single map takes the same with all three (512^3 50 us, the
+// map read from HBM while the passes before are written back).
+constexpr int BITS_U = 4;
+
+__device__ __forceinline__ void map_bits(const uint8_t* __restrict__ occ, int64_t n, int64_t c0,
                                          uint32_t* __restrict__ bits)
 {
     const int mis = misalignment(occ);
-    const int64_t f = 32 * u - mis;   // the word's first voxel
-    if (f >= n) return;
-    uint32_t m = 0;
-    if (f >= 0 && f + 32 <= n) {
-        const uint4* p = reinterpret_cast<const uint4*>(occ + f);
-        const uint4 a = p[0], b = p[1];
-        const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    const int lane = threadIdx.x & 63;
+    const int64_t f0 = 16 * c0 - mis;   // the wave's first voxel
+    if (f0 >= n) return;
+    uint4 v[BITS_U];
+    uint32_t m[BITS_U];
+    const bool whole = f0 >= 0 && f0 + 1024 * BITS_U <= n;   // wave-uniform
+    if (whole) {
+        const uint4* p = reinterpret_cast<const uint4*>(occ + f0) + lane;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            // the eight 0x80 flags of two words, weighted 1 .. 128: 128 times their bits
-            uint32_t t = __builtin_amdgcn_udot4(nonzero_high(w[2 * k]), 0x08040201u, 0u, false);
-            t = __builtin_amdgcn_udot4(nonzero_high(w[2 * k + 1]), 0x80402010u, t, false);
-            m |= (t >> 7) << (8 * k);
-        }
+        for (int j = 0; j < BITS_U; ++j) v[j] = p[64 * j];
+#pragma unroll
+        for (int j = 0; j < BITS_U; ++j) m[j] = chunk_bits(v[j]);
     } else {
-        for (int k = 0; k < 32; ++k)
-            if (f + k >= 0 && f + k < n && occ[f + k]) m |= 1u << k;
+#pragma unroll
+        for (int j = 0; j < BITS_U; ++j) {
+            const int64_t f = f0 + 1024 * j + 16 * lane;
+            m[j] = 0;
+            if (f >= 0 && f + 16 <= n) {
+                m[j] = chunk_bits(*reinterpret_cast<const uint4*>(occ + f));
+            } else {
+                for (int k = 0; k < 16; ++k)
+                    if (f + k >= 0 && f + k < n && occ[f + k]) m[j] |= 1u << k;
+            }
+        }
     }
-    bits[u] = m;
+    uint32_t* w = bits + c0 / 2;
+#pragma unroll
+    for (int j = 0; j < BITS_U; ++j) {
+        // quad_perm 1, 1, 3, 3: the neighbour of an even lane
+        const uint32_t o = __builtin_amdgcn_update_dpp(0, m[j], 0xF5, 0xF, 0xF, true);
+        if ((lane & 1) == 0 && f0 + 1024 * j + 16 * lane < n) w[32 * j + lane / 2] = m[j] | o << 16;
+    }
 }
 
 // Squared distances between block b (positions 8 b .. 8 b + 7) and group g of a
