@@ -149,7 +149,11 @@ __global__ void k_logodds_rays(GridArgs g, const float* __restrict__ pts, int64_
     }
     if (near) {
         constexpr float SURE = 0.999f;
-        auto crossed = [&](int k) { return step[k] != 0 ? (int)rintf((tm[k] - t0[k]) * len[k]) : 0; };
+        // never more than the axis has left: one shorter than 2.9e-39 voxels has
+        // an infinite parameter step, so an infinite product after its crossing
+        auto crossed = [&](int k) {
+            return step[k] != 0 ? (int)fminf(rintf((tm[k] - t0[k]) * len[k]), (float)left[k]) : 0;
+        };
         float m = fminf(fminf(tm[0], tm[1]), tm[2]);
         while (m < SURE && max(max(enter[0], enter[1]), enter[2]) > 0) {
             const bool cx = tm[0] == m, cy = !cx && tm[1] == m, cz = !cx && !cy;
