@@ -38,8 +38,14 @@ constexpr int ROW_ALIGN = 64;
 
 __host__ __device__ inline int padded_rows(int b) { return (b + ROW_ALIGN - 1) / ROW_ALIGN * ROW_ALIGN; }
 
-// float -> bfloat16 bits, round to nearest even (one v_cvt_pk_bf16_f32)
-__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+// float -> bfloat16 bits, round to nearest even, one v_cvt_pk_bf16_f32: a NaN
+// keeps its sign and the upper bits of its payload.  For values that stay on
+// chip, where only being NaN matters (with f2bf there the inference takes 110
+// instead of 85 us for 262,144 states).
+__device__ __forceinline__ uint16_t cvt_bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+
+// The same for values that go to memory: every NaN is stored as 0x7FC0.
+__device__ __forceinline__ uint16_t f2bf(float f) { return f != f ? (uint16_t)0x7FC0u : cvt_bf(f); }
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -475,7 +481,7 @@ __global__ __launch_bounds__(512) void k_mlp_infer(const uint16_t* __restrict__ 
                 uint32_t v = 0;
                 if (b < batch) {
                     const float a = q[(size_t)b * SDF_MLP_JOINTS + j];
-                    v = (uint32_t)f2bf(sinf(a)) | ((uint32_t)f2bf(cosf(a)) << 16);
+                    v = (uint32_t)cvt_bf(sinf(a)) | ((uint32_t)cvt_bf(cosf(a)) << 16);
                 }
                 o[j] = v;
             } else {
@@ -526,7 +532,7 @@ __global__ __launch_bounds__(512) void k_mlp_infer(const uint16_t* __restrict__ 
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const float z = acc[j][e] + bv[j][e];
-                        v[e] = f2bf((z > 0.0f || z != z) ? z : 0.0f);
+                        v[e] = cvt_bf((z > 0.0f || z != z) ? z : 0.0f);
                     }
                     *reinterpret_cast<uint2*>(O + (16 * i + r) * ACT_LD + n0 + 16 * j + g4) = pack4(v);
                 }
