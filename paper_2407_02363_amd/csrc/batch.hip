@@ -347,20 +347,28 @@ int make_plan(const edt_batch_map_t* maps, int n, int txy, int tz, BatchPlan& p)
     return EDT_OK;
 }
 
-EdtTuning batch_default(int nx, int ny, int nz)
+// Tiles of the general persistent kernel, for the longest axes of a batch.  A
+// work-group's local memory grows with tile width times line length, and with
+// it falls the number of work-groups per CU, while narrow tiles give every band
+// fewer columns.  All six tile pairs timed on random maps of 0.1% / 2%:
+//   z 64 against 32 columns up to 192 slices (4 maps 100 x 100 x 192: 267 / 285
+//   against 294 / 308 us; at 208: 297 / 334 against 312 / 318);
+//   z 16 against 32 past 320 slices with at most 320 rows (2 maps 240 x 240 x 400:
+//   935 / 985 against 1031 / 1138; at 320 slices 847 / 892 against 697 / 740), not
+//   with more rows (512^3: 2971 / 3215 against 2586 / 2851);
+//   xy 32 against 16 columns on every shape (4 maps 300^3 with z 32: 2022 / 2162
+//   against 2859 / 3033).
+EdtTuning batch_default(int ny, int nz)
 {
-    edt_grid_t g{nx, ny, nz, {0.0f, 0.0f, 0.0f}, 1.0f};
-    EdtTuning t = default_tuning(&g);
-    if (t.xy_tw > 32) t.xy_tw = 32;
-    if (t.z_tw < 16) t.z_tw = 16;
-    return t;
+    const int z = nz <= 192 ? 64 : (nz > 320 && ny <= 320 ? 16 : 32);
+    return EdtTuning{32, z, 256, 256};
 }
 
 EdtTuning batch_current(int n, int nx, int ny, int nz, bool lean_ok)
 {
     EdtTuning t;
     if (tuned_lookup(1, n, nx, ny, nz, t) && (t.xy_tw != 64 || lean_ok)) return t;
-    return lean_ok ? EdtTuning{64, 64, 512, 512} : batch_default(nx, ny, nz);
+    return lean_ok ? EdtTuning{64, 64, 512, 512} : batch_default(ny, nz);
 }
 
 template <int TXY, int TZ>
