@@ -414,8 +414,10 @@ size_t edt_batch_workspace_bytes(int32_t n_maps);
  *   tuning  NULL = the batch autotuner's choice for this shape class, else
  *           xy_tile in {16, 32}, z_tile in {16, 32, 64} (z_group, xy_group ignored:
  *           batches use 256-thread work-groups), or xy_tile = z_tile = 64: the
- *           banded lean tiles (512-thread work-groups; every
- *           axis at most 512, nz at least 1).
+ *           banded lean tiles (512-thread work-groups; every axis at most 512,
+ *           rows of 64 voxels or more, at most 256 rows and 128 slices).  What
+ *           edt_default_tuning answers is accepted for every batch: 64 / 64 with
+ *           xy_group 512 and z_group 256 means NULL past the lean tiles' limits.
  * Errors: EDT_ERR_UNSUPPORTED for an axis above 512 or tiles that do not
  * fit; argument errors as for edt_compute.
  */

@@ -478,7 +478,12 @@ int batch_common(const edt_batch_map_t* maps, int32_t n_maps, void* ws, size_t w
         nz = std::max(nz, maps[i].grid.nz);
     }
     const bool lean_ok = lean_batch_ok(maps, n_maps);
-    if (tuning) {
+    // edt_default_tuning's answer for a map up to 512 per axis names the search
+    // tiles, which a batch does not have: past the lean tiles it means the
+    // batch's own choice
+    const bool search = tuning && tuning->xy_tile == 64 && tuning->xy_group == 512 && tuning->z_tile == 64 &&
+                        tuning->z_group == 256;
+    if (tuning && !(search && !lean_ok)) {
         t.xy_tw = tuning->xy_tile;
         t.z_tw = tuning->z_tile;
         t.z_nt = 256;

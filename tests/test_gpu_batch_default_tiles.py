@@ -51,3 +51,31 @@ def test_default_tiles(oracle_lib, shapes, kernel):
         rd2, rsite = oracle_lib.edt(x)
         assert np.array_equal(a.cpu().numpy().reshape(x.shape), rd2)
         assert np.array_equal(b.cpu().numpy().reshape(x.shape), rsite)
+
+
+@pytest.mark.parametrize("shape", [(20, 257, 64), (30, 30, 63), (129, 20, 64), (257, 300, 9), (2, 2, 2), (64, 64, 64)])
+def test_the_default_tuning_of_a_map_serves_a_batch(oracle_lib, shape):
+    """What edt_default_tuning answers for a map is accepted for a batch of
+    such maps, with and without a workspace; 64 / 64 without the groups stays
+    the lean tiles, refused past their limits."""
+    say("batch with the map's tuning", shape)
+    nz, ny, nx = shape
+    tiles = edt.edt_default_tuning(grid_of(shape))
+    occs, maps, (o, d2, st) = batch([shape] * 3, 60)
+    ws = edt.new_batch_workspace(3, dev())
+    refs = [oracle_lib.edt(x) for x in occs]
+    for call in (lambda: edt.edt_compute_batched(maps, ws, tiles), lambda: edt.edt_compute_batched_noalloc(maps, tiles)):
+        for a in d2 + st:
+            a.fill_(-7)
+        call()
+        torch.cuda.synchronize()
+        for x, a, b, (rd2, rsite) in zip(occs, d2, st, refs):
+            assert np.array_equal(a.cpu().numpy().reshape(x.shape), rd2)
+            assert np.array_equal(b.cpu().numpy().reshape(x.shape), rsite)
+    if nx >= 64 and ny <= 256 and nz <= 128:
+        edt.edt_compute_batched(maps, ws, (64, 64))
+    else:
+        for refused in ((64, 64), (64, 64, 256, 256)):
+            with pytest.raises(edt.EdtError) as e:
+                edt.edt_compute_batched(maps, ws, refused)
+            assert e.value.status == -5
