@@ -7,27 +7,20 @@
 // fixed-point sums, so independent of the order of accumulation); keep i
 // iff d_i <= mu + alpha * sigma.
 //
-// Neighbour search: cells slightly larger than R (1.001 R), so every
-// neighbour within R lies in the 3 x 3 x 3 cells around a point for
-// coordinates below about 80 m.  The table is the grid of cells wrapped onto
-// A x B x C buckets (powers of two, each at least 8): cells that differ by
-// whole periods share a bucket, the 27 cells around any cell fall into
-// distinct buckets, and the cells of an x run into consecutive ones.  Points
-// are counted per bucket, every bucket gets a place in the sorted points, and
-// the points are scattered there, so the points of an x run of cells are one
-// contiguous range (two where the run wraps).
+// Neighbour search: a grid of cells wrapped onto A x B x C buckets (powers of
+// two, each at least 8).  Cells that differ by whole periods share a bucket, the
+// cells around any cell fall into distinct buckets, and the cells of an x run
+// into consecutive ones.  Points are counted per bucket, every bucket gets a
+// place in the sorted points, and the points are scattered there, so the points
+// of an x run of cells are one contiguous range (two where the run wraps).
 //
-// One thread per point in bucket order.  Read lane by lane from memory, the
-// candidates (about 90 a point, each lane at its own place) cost the texture
-// unit 80 cycles per load instruction, 205 us in all.  So a wave first copies
-// what its points need into LDS: its points lie in two or three rows of cells,
-// and the points of a row's x range in each of the nine rows around it are one
-// contiguous range.  Each lane then streams its own nine ranges from LDS four
-// candidates at a time, the next four in flight, and keeps the k smallest
-// squared distances sorted in registers, one median per kept value and
-// candidate.  307,200 points: 252 us with cells of R / 2 read from memory (26
-// runs, each two dependent loads and at least eight candidate slots), 82 us
-// like this.
+// k_sor_knn holds two searches with the same results, the faster one chosen on
+// the device from the cloud's density (k_sor_zero):
+//   * cells of 1.001 R: every neighbour lies in the 3 x 3 x 3 cells around a point,
+//     which takes all their points, from local memory;
+//   * for dense clouds cells of 1.001 R / 2: 5 x 5 x 5 cells, nearest first, cells
+//     beyond the k-th nearest point left out (search_dense).
+// The 0.1% covers the rounding of coordinates below about 80 m.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -106,12 +99,70 @@ __device__ __forceinline__ unsigned bucket(int ix, int iy, int iz, const Wrap& w
 // sorted points given out.
 constexpr int ACC_SLOTS = 64, ACC_LINE = 16;
 constexpr int ACC_GIVEN = ACC_SLOTS * ACC_LINE;
+constexpr int ACC_DENSE = ACC_GIVEN + 1;   // 1: cells of R / 2 and search_dense
 
-__global__ void k_sor_zero(uint4* __restrict__ count, int T4, unsigned long long* __restrict__ acc)
+// search_dense takes over where a point's cell of 3 R holds more than DENSE other
+// points on average, about the candidates the other search would take.  The whole
+// filter with that one and with search_dense, us, by this average: a frame of
+// 307,200 points 115 against 189 at 2, 217 / 193 at 59, 360 / 211 at 225, 605 / 395
+// at 795; 200,000 points in a volume 90 / 137 at 146, 180 / 113 at 595; 100,000
+// points in a ball 2,000 / 480 at 7,900.
+constexpr float DENSE = 180.0f;
+// Up to FEW points the first search is the faster one or close to it at any
+// density (1,000 points in a ball: 120 / 107 to 160 / 350), and goes without the
+// estimate's 4 us.
+constexpr int FEW = 2048;
+constexpr int SAMPLES = 1024, SLOTS = 2 * SAMPLES;
+
+// Clears the counters.  With est = 1, work-group 0 meanwhile estimates the
+// density: it counts the pairs of SAMPLES evenly spread points (one per thread, step
+// points apart) that share a cell of 3 R, in a hash table in local memory.
+__global__ __launch_bounds__(SAMPLES) void k_sor_zero(uint4* __restrict__ count, int T4,
+                                                      unsigned long long* __restrict__ acc, int est,
+                                                      const float* __restrict__ pts, int64_t n, int64_t step, float R)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < T4) count[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (i <= ACC_GIVEN) acc[i] = 0ull;
+    __shared__ __attribute__((aligned(16))) unsigned table[2][SLOTS];   // keys, points
+    __shared__ unsigned pairs;
+    const int t = threadIdx.x;
+    if ((int)blockIdx.x >= est) {
+        const int i = ((int)blockIdx.x - est) * SAMPLES + t;
+        if (i < T4) count[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (i <= ACC_DENSE - est) acc[i] = 0ull;
+        return;
+    }
+    const int m = (int)min(n, (int64_t)SAMPLES);
+    float p[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) p[c] = t < m ? pts[3 * (t * step) + c] : __builtin_nanf("");
+    reinterpret_cast<uint4*>(table)[t] = make_uint4(0u, 0u, 0u, 0u);
+    if (t == 0) pairs = 0u;
+    __syncthreads();
+    if (finite3(p[0], p[1], p[2])) {
+        unsigned key = 0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) key = (key ^ (unsigned)cell_of(p[c], 3.0f * R)) * 0x9E3779B1u + (key >> 15);
+        key |= 1u;
+        for (unsigned at = key >> 16;; ++at) {   // at most SAMPLES of the SLOTS are taken
+            const unsigned old = atomicCAS(&table[0][at % SLOTS], 0u, key);
+            if (old == 0u || old == key) {
+                const unsigned others = atomicAdd(&table[1][at % SLOTS], 1u);
+                if (others) atomicAdd(&pairs, others);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    if (t == 0) {
+        const float others = m > 1 ? 2.0f * (float)pairs / ((float)m * (float)(m - 1)) * (float)n : 0.0f;
+        acc[ACC_DENSE] = others > DENSE ? 1ull : 0ull;
+    }
+}
+static_assert(2 * SLOTS == 4 * SAMPLES, "one 16-byte store per thread clears the table");
+
+// Cell size: h1, or half of it for search_dense.
+__device__ __forceinline__ float cell_size(float h1, const unsigned long long* acc)
+{
+    return acc[ACC_DENSE] ? 0.5f * h1 : h1;
 }
 
 // Neighbouring points of a frame tend to share a bucket, and atomics on one
@@ -146,8 +197,9 @@ __device__ __forceinline__ Run same_bucket_run(unsigned b)
 
 // Counts the finite points per bucket; a point that is not finite gets its
 // mean distance (NaN) here, since the neighbour search never sees it.
-__global__ void k_sor_count(const float* __restrict__ pts, int64_t n, float h, Wrap w,
-                            unsigned* __restrict__ count, float* __restrict__ dmean)
+__global__ void k_sor_count(const float* __restrict__ pts, int64_t n, float h1, Wrap w,
+                            unsigned* __restrict__ count, float* __restrict__ dmean,
+                            const unsigned long long* __restrict__ acc)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -156,6 +208,7 @@ __global__ void k_sor_count(const float* __restrict__ pts, int64_t n, float h, W
         dmean[i] = __builtin_nanf("");
         return;
     }
+    const float h = cell_size(h1, acc);
     const unsigned b = bucket(cell_of(x, h), cell_of(y, h), cell_of(z, h), w);
     const Run r = same_bucket_run(b);
     if (r.first) atomicAdd(count + b, (unsigned)r.n);
@@ -204,14 +257,15 @@ __global__ __launch_bounds__(256) void k_sor_place(const uint4* __restrict__ cou
 }
 
 // Takes the places of a bucket from its last one down: count is used up.
-__global__ void k_sor_scatter(const float* __restrict__ pts, int64_t n, float h, Wrap w,
+__global__ void k_sor_scatter(const float* __restrict__ pts, int64_t n, float h1, Wrap w,
                               const uint2* __restrict__ table, unsigned* __restrict__ count,
-                              float4* __restrict__ spts)
+                              float4* __restrict__ spts, const unsigned long long* __restrict__ acc)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float x = pts[3 * i], y = pts[3 * i + 1], z = pts[3 * i + 2];
     if (!finite3(x, y, z)) return;
+    const float h = cell_size(h1, acc);
     const unsigned b = bucket(cell_of(x, h), cell_of(y, h), cell_of(z, h), w);
     const Run r = same_bucket_run(b);
     unsigned left = 0;   // points of the bucket still to place before the run's
@@ -227,22 +281,189 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
     return v;
 }
 
+// The mean distance from the k smallest squared distances, in ascending order.
+template <int K>
+__device__ __forceinline__ float mean_distance(const float (&best)[K], int found, int k, float R)
+{
+    const int m = min(found, k);
+    float sum = 0.0f;
+#pragma unroll
+    for (int u = 0; u < K; ++u)
+        if (u < m) sum = sum + sqrtf(best[u]);
+    sum = sum + (float)(k - m) * R;
+    return sum / (float)k;
+}
+
+// A wave's share of the statistics: integer sums, reduced per wave before one
+// atomic addition per wave, so the order of the waves does not matter.
+__device__ __forceinline__ void add_statistics(bool active, float d, unsigned long long* __restrict__ acc)
+{
+    const double dd = (double)d;
+    const unsigned long long a1 = wave_sum(active ? (unsigned long long)(long long)rint(dd * SCALE1) : 0ull);
+    const unsigned long long a2 = wave_sum(active ? (unsigned long long)(long long)rint(dd * dd * SCALE2) : 0ull);
+    const unsigned long long a3 = wave_sum(active ? 1ull : 0ull);
+    if ((threadIdx.x & 63) == 0 && a3) {
+        unsigned long long* a = acc + (blockIdx.x % ACC_SLOTS) * ACC_LINE;
+        atomicAdd(a + 0, a1);
+        atomicAdd(a + 1, a2);
+        atomicAdd(a + 2, a3);
+    }
+}
+
+// The search for clouds with many points per cell of R, where taking all points
+// of 27 such cells costs more than looking for the near ones.  One thread per
+// finite point in bucket order.  A query visits its own cell, then the 25 x runs
+// (dy, dz in -2..2) of the 5 x 5 x 5 cells around it, nearest first, each run a
+// contiguous range of cells dx in lo..hi (its own cell left out of the own run).
+// Exact as above.  Once k neighbours are in hand, a cell whose box (widened by a
+// rounding slack) lies farther than the current k-th nearest is left out: its
+// points cannot change the k smallest distances, and the count m = min(found, k)
+// is already k.  The visiting order changes nothing: the k smallest values are
+// summed in ascending order.  Bound by the latency of the candidates' loads.
+template <int K>
+__device__ __forceinline__ float search_dense(const float4 P, int k, float R, float h, const Wrap& w,
+                                              const uint2* __restrict__ table, const float4* __restrict__ spts)
+{
+    const int i = __float_as_int(P.w);
+    const float px = P.x, py = P.y, pz = P.z;
+    const float rr = R * R;
+    const int cx = cell_of(px, h), cy = cell_of(py, h), cz = cell_of(pz, h);
+    // a point's cell can differ from its coordinates' box by rounding;
+    // the pruning bound below is shrunk by this slack
+    const float slack = 1e-4f * h + 1e-6f * (fabsf(px) + fabsf(py) + fabsf(pz));
+    float best[K];
+#pragma unroll
+    for (int u = 0; u < K; ++u) best[u] = __builtin_huge_valf();
+    int found = 0;
+    // candidates e .. e + 3 of a range that ends at e1
+    auto take = [&](const float4 (&q)[4], unsigned e, unsigned e1) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (e + u >= e1 || __float_as_int(q[u].w) == i) continue;
+            const float ex = q[u].x - px, ey = q[u].y - py, ez = q[u].z - pz;
+            const float sd = (ex * ex + ey * ey) + ez * ez;
+            if (!(sd <= rr)) continue;
+            ++found;
+            // no smaller than the largest kept value: best[] would not change
+            if (sd >= best[K - 1]) continue;
+#pragma unroll
+            for (int v = K - 1; v > 0; --v) best[v] = __builtin_amdgcn_fmed3f(best[v - 1], best[v], sd);
+            best[0] = fminf(best[0], sd);
+        }
+    };
+    // two sets of four candidates in turn, the next one in flight: the local memory
+    // of the other search leaves only 13 waves per CU to cover the loads
+    auto scan = [&](unsigned e0, unsigned e1) {
+        if (e0 >= e1) return;
+        float4 qa[4], qb[4];
+        auto fetch = [&](float4 (&q)[4], unsigned e) {
+            if (e < e1) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) q[u] = spts[min(e + u, e1 - 1)];
+            }
+        };
+        fetch(qa, e0);
+        for (unsigned e = e0; e < e1; e += 8) {
+            fetch(qb, e + 4);
+            take(qa, e, e1);
+            fetch(qa, e + 8);
+            take(qb, e + 4, e1);
+        }
+    };
+    // the cells x0..x1 (offsets from cx, x0 <= x1) of one row: one range,
+    // or two where the run wraps round the table
+    auto scan_cells = [&](unsigned row, int x0, int x1) {
+        const unsigned xs = (unsigned)(cx + x0) & w.mx, xe = (unsigned)(cx + x1) & w.mx;
+        const bool wraps = xs > xe;
+        const uint2 c = table[row | (wraps ? w.mx : xe)];
+        unsigned r0 = table[row | xs].x, r1 = c.x + c.y, s0 = 0, s1 = 0;
+        if (wraps) {
+            const uint2 b = table[row | xe];
+            s0 = table[row].x;
+            s1 = b.x + b.y;
+        }
+#pragma unroll 1
+        for (int part = 0; part < 2; ++part) {
+            scan(r0, r1);
+            r0 = s0;
+            r1 = s1;
+        }
+    };
+    // distance from the point to the box of the cell at offset o along one
+    // axis (0 for its own cell), less the slack
+    auto gap = [&](int o, int cc, float pp) {
+        const float lo = (float)(cc + o) * h, hi = (float)(cc + o + 1) * h;
+        const float gg = o < 0 ? pp - hi : (o > 0 ? lo - pp : 0.0f);
+        return fmaxf(gg - slack, 0.0f);
+    };
+    auto kth = [&]() {
+        float v = __builtin_huge_valf();
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+            if (u == k - 1) v = best[u];
+        return found >= k ? v : __builtin_huge_valf();
+    };
+    // the own cell
+    scan_cells(bucket(0, cy, cz, w), 0, 0);
+    // the 25 runs, nearest first: (dy, dz) by |dy| + |dz|, then max
+    constexpr int RY[25] = {0, -1, 1, 0, 0, -1, 1, -1, 1, -2, 2, 0, 0, -2, 2, -2, 2, -1, 1, -1, 1, -2, 2, -2, 2};
+    constexpr int RZ[25] = {0, 0, 0, -1, 1, -1, -1, 1, 1, 0, 0, -2, 2, -1, -1, 1, 1, -2, -2, 2, 2, -2, -2, 2, 2};
+#pragma unroll 1
+    for (int r = 0; r < 25; ++r) {
+        const int oy = RY[r], oz = RZ[r];
+        const float gy = gap(oy, cy, py), gz = gap(oz, cz, pz);
+        const float base = gy * gy + gz * gz;
+        const float kb = kth();
+        if (base > kb) continue;
+        // the x offsets still within reach: gaps grow with |dx|
+        int x0 = -2, x1 = 2;
+        while (x0 < 0) {
+            const float g = gap(x0, cx, px);
+            if (base + g * g <= kb) break;
+            ++x0;
+        }
+        while (x1 > 0) {
+            const float g = gap(x1, cx, px);
+            if (base + g * g <= kb) break;
+            --x1;
+        }
+        const unsigned row = bucket(0, cy + oy, cz + oz, w);
+        if (r == 0) {   // the own run without the own cell
+            if (x0 < 0) scan_cells(row, x0, -1);
+            if (x1 > 0) scan_cells(row, 1, x1);
+        } else {
+            scan_cells(row, x0, x1);
+        }
+    }
+    return mean_distance(best, found, k, R);
+}
+
 // One thread per finite point, points in bucket order (neighbouring cells
 // sit side by side in spts, so a wave's points share candidate ranges).  A
 // query takes the nine x runs (dy, dz in -1..1) of the 3 x 3 x 3 cells around
 // it.  That is exact: a point within R lies in one of the 27 cells, whose
 // ranges are disjoint, so it is counted once; candidates from cells a whole
-// period away lie farther than R and fail the radius test.  Once k neighbours
-// are in hand, a run whose cells (widened by a rounding slack) lie farther than
-// the current k-th nearest is left out: its points cannot change the k
-// smallest distances, and the count m = min(found, k) is already k.  The
-// visiting order changes nothing: the k smallest values are summed in ascending
-// order, and the statistics are integer sums, reduced per wave before one
-// atomic add per wave.
+// period away lie farther than R and fail the radius test.
+//
+// Read lane by lane from memory, the candidates (about 65 a point in a depth
+// frame, each lane at its own place) cost the texture unit 80 cycles per load
+// instruction, 205 us in all.  So a wave first copies what its points need into
+// LDS: its points lie in two or three rows of cells, and the points of a row's x
+// range in each of the nine rows around it are one contiguous range.  Each lane
+// then streams its own nine ranges from LDS four candidates at a time, the next
+// four in flight, and keeps the k smallest squared distances sorted in registers,
+// one median per kept value and candidate.  307,200 points of a depth frame, R =
+// 1 cm: 77 us of the filter's 116.
+//
 // Points a wave's LDS holds; a wave that needs more reads from memory.  307,200
 // points, the whole filter: 116-124 us with 768, 131 with 1024, 148 with 1536 (fewer
 // waves per CU).
 constexpr int CAP = 768;
+// Rows of cells up to which a wave copies: it takes them one after the other, a
+// load's latency each, and points that share few rows' candidates gain little.  The
+// whole filter with no limit / 16 / 8 / 4: 20,000 points of a frame 52 / 52 / 46 /
+// 42 us, 307,200 with R = 5 mm 106 / 100 / 93 / 90, with R = 1 cm 116 with any.
+constexpr int COPY_ROWS = 4;
 static_assert(3 * CAP >= 36 * 64, "18 ranges per lane");
 
 template <int K>
@@ -260,9 +481,17 @@ __global__ __launch_bounds__(64) void k_sor_knn(int k, float R, float h, Wrap w,
     const unsigned t = blockIdx.x * 64u + lane;
     const unsigned nfin = (unsigned)acc[ACC_GIVEN];
     const bool active = t < nfin;
-    unsigned long long a1 = 0, a2 = 0, a3 = 0;
+    float d = 0.0f;
     const float4 P = active ? spts[t] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     const int i = __float_as_int(P.w);
+    if (acc[ACC_DENSE]) {
+        if (active) {
+            d = search_dense<K>(P, k, R, 0.5f * h, w, table, spts);
+            dmean[i] = d;
+        }
+        add_statistics(active, d, acc);
+        return;
+    }
     const float px = P.x, py = P.y, pz = P.z;
     const float rr = R * R;
     const int cx = cell_of(px, h), cy = cell_of(py, h), cz = cell_of(pz, h);
@@ -287,7 +516,8 @@ __global__ __launch_bounds__(64) void k_sor_knn(int k, float R, float h, Wrap w,
     // the first lane's first cell to the last lane's last
     const unsigned key = bucket(0, cy, cz, w);
     int used = 0, nr = 0, self = 0;
-    bool fits = true;
+    const unsigned before = __shfl_up(key, 1, 64);   // lanes of a row follow each other
+    bool fits = __popcll(__ballot(active && (lane == 0 || before != key))) <= COPY_ROWS;
     for (uint64_t todo = __ballot(active); todo && fits;) {
         const int first = __ffsll((unsigned long long)todo) - 1;
         const unsigned gk = __builtin_amdgcn_readlane(key, first);
@@ -422,28 +652,10 @@ __global__ __launch_bounds__(64) void k_sor_knn(int k, float R, float h, Wrap w,
                 for (int u = 0; u < 4; ++u) take(q[u].x, q[u].y, q[u].z, e + u < g1 && __float_as_int(q[u].w) != i);
             }
         }
-        const int m = min(found, k);
-        float sum = 0.0f;
-#pragma unroll
-        for (int u = 0; u < K; ++u)
-            if (u < m) sum = sum + sqrtf(best[u]);
-        sum = sum + (float)(k - m) * R;
-        const float d = sum / (float)k;
+        d = mean_distance(best, found, k, R);
         dmean[i] = d;
-        const double dd = (double)d;
-        a1 = (unsigned long long)(long long)rint(dd * SCALE1);
-        a2 = (unsigned long long)(long long)rint(dd * dd * SCALE2);
-        a3 = 1ull;
     }
-    a1 = wave_sum(a1);
-    a2 = wave_sum(a2);
-    a3 = wave_sum(a3);
-    if ((threadIdx.x & 63) == 0 && a3) {
-        unsigned long long* a = acc + (blockIdx.x % ACC_SLOTS) * ACC_LINE;
-        atomicAdd(a + 0, a1);
-        atomicAdd(a + 1, a2);
-        atomicAdd(a + 2, a3);
-    }
+    add_statistics(active, d, acc);
 }
 
 // By whole waves: lane l adds up slot l.
@@ -535,23 +747,25 @@ int edt_outlier_filter(const float* pts, int64_t n, int32_t k, float radius, flo
     const float h = radius * 1.001f;
     const hipStream_t st = as_stream(stream);
     const unsigned pblocks = (unsigned)((std::max<int64_t>(n, 1) + 255) / 256);
-    hipLaunchKernelGGL(k_sor_zero, dim3((std::max(T / 4, ACC_GIVEN + 1) + 255) / 256), dim3(256), 0, st, reinterpret_cast<uint4*>(count), T / 4, acc);
+    const int est = n > FEW ? 1 : 0;
+    hipLaunchKernelGGL(k_sor_zero, dim3(est + (std::max(T / 4, ACC_DENSE + 1) + SAMPLES - 1) / SAMPLES), dim3(SAMPLES), 0, st,
+                       reinterpret_cast<uint4*>(count), T / 4, acc, est, pts, n, std::max<int64_t>(1, n / SAMPLES), radius);
     int rc = check_launch("k_sor_zero");
     if (rc) return rc;
     if (n > 0) {
-        hipLaunchKernelGGL(k_sor_count, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, count, dm);
+        hipLaunchKernelGGL(k_sor_count, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, count, dm, acc);
         if ((rc = check_launch("k_sor_count"))) return rc;
         hipLaunchKernelGGL(k_sor_place, dim3((T / 4 + 256 * PLACE_PER - 1) / (256 * PLACE_PER)), dim3(256), 0, st,
                            reinterpret_cast<const uint4*>(count), T / 4, reinterpret_cast<uint4*>(table), acc);
         if ((rc = check_launch("k_sor_place"))) return rc;
-        hipLaunchKernelGGL(k_sor_scatter, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, table, count, spts);
+        hipLaunchKernelGGL(k_sor_scatter, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, table, count, spts,
+                           acc);
         if ((rc = check_launch("k_sor_scatter"))) return rc;
+        const dim3 waves((unsigned)((n + 63) / 64));
         if (k <= 8)
-            hipLaunchKernelGGL(k_sor_knn<8>, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, (int)k, radius, h, L.wrap, table, spts,
-                               dm, acc);
+            hipLaunchKernelGGL(k_sor_knn<8>, waves, dim3(64), 0, st, (int)k, radius, h, L.wrap, table, spts, dm, acc);
         else
-            hipLaunchKernelGGL(k_sor_knn<KMAX>, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, (int)k, radius, h, L.wrap, table,
-                               spts, dm, acc);
+            hipLaunchKernelGGL(k_sor_knn<KMAX>, waves, dim3(64), 0, st, (int)k, radius, h, L.wrap, table, spts, dm, acc);
         if ((rc = check_launch("k_sor_knn"))) return rc;
     }
     hipLaunchKernelGGL(k_sor_keep, dim3(pblocks), dim3(256), 0, st, pts, n, dm, acc, (double)alpha,
