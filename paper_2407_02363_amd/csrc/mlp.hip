@@ -35,6 +35,7 @@ constexpr int HID = SDF_MLP_HIDDEN;
 constexpr int INP = SDF_MLP_IN_PAD;
 constexpr int OUTP = SDF_MLP_OUT_PAD;
 constexpr int ROW_ALIGN = 64;
+constexpr int TRAIN_ROWS = 8192;   // the most rows that the backward pass takes
 
 __host__ __device__ inline int padded_rows(int b) { return (b + ROW_ALIGN - 1) / ROW_ALIGN * ROW_ALIGN; }
 
@@ -82,6 +83,14 @@ __host__ __device__ inline WsLayout ws_layout(int P)
     w.h2 = take(hid);
     w.h3 = take(hid);
     w.y = take((size_t)P * OUTP * 4);
+    if (P > TRAIN_ROWS) {
+        // nothing of what only the backward pass reads, but no less than a
+        // smaller batch on the same workspace needs
+        w.dy = w.xt = w.h1t = w.h2t = w.h3t = w.dyt = w.d1t = w.d2t = w.d3t = w.w2t = w.w3t = w.w4t = w.part = w.gpart = o;
+        const size_t train = ws_layout(TRAIN_ROWS).total;
+        w.total = o > train ? o : train;
+        return w;
+    }
     w.dy = take((size_t)P * OUTP * 2);
     w.xt = take(INP * row_t);
     w.h1t = take(HID * row_t);
@@ -100,8 +109,7 @@ __host__ __device__ inline WsLayout ws_layout(int P)
     return w;
 }
 
-constexpr int MT = 1;             // 16-row tiles per work-group of the training passes (2: 17.3 against 15.0 us)
-constexpr int RB = 16 * MT;       // rows per work-group
+constexpr int TRAIN_MT = 1;         // 16-row tiles per work-group of the training passes (2: 17.3 against 15.0 us)
 constexpr int ACT_LD = HID + 8;   // LDS row stride of activations (bf16): rows 4 banks apart
 
 __device__ __forceinline__ bf16x8 load8(const uint16_t* p)
@@ -153,6 +161,7 @@ __device__ __forceinline__ uint2 pack4(const uint16_t (&v)[4])
 }
 
 // 32 features of the work-group's rows (LDS, row stride ACT_LD) to [feature][P].
+template <int MT>
 __device__ __forceinline__ void transpose32(const uint16_t* a, uint16_t* out, int P, int row0)
 {
     const int t = threadIdx.x;
@@ -170,25 +179,29 @@ __device__ __forceinline__ void transpose32(const uint16_t* a, uint16_t* out, in
 // [32 w, 32 w + 32) of every hidden layer and loads its weights of all four
 // layers at once (150 registers): they depend on nothing, so only the four
 // products and their barriers are serial.  Every row's x, h1, h2, h3 (row-major
-// and transposed) and y go to the workspace.  A state index outside [0,
-// n_rows) gives its row NaN inputs; rows past the batch are zero inputs.
+// and, for the backward pass, transposed) and y go to the workspace.  Batches
+// beyond what the backward pass takes: 64 rows per work-group (MT = 4).  A state
+// index outside [0, n_rows) gives its row NaN inputs; rows past the batch are zero
+// inputs.
 struct FwdOut {
     uint16_t *x, *h[3], *xt, *ht[3];
     float* y32;
     float* y;   // nullable, [batch][12]
 };
 
+template <int MT>
 __global__ __launch_bounds__(512) void k_mlp_forward(const uint16_t* __restrict__ w16,
                                                      const float* __restrict__ master,
                                                      const float* __restrict__ q, int n_rows,
                                                      const int* __restrict__ idx, int batch, int P, FwdOut o)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t act[2][RB * ACT_LD];
+    constexpr bool SAVE_T = MT == TRAIN_MT;   // the transposed copies are the backward pass's
+    __shared__ __attribute__((aligned(16))) uint16_t act[2][16 * MT * ACT_LD];
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int block = xcd_block(blockIdx.x, P / RB);
-    if (block >= P / RB) return;
-    const int row0 = block * RB;
+    const int block = xcd_block(blockIdx.x, P / (16 * MT));
+    if (block >= P / (16 * MT)) return;
+    const int row0 = block * 16 * MT;
     const int n0 = wave * 32;
     const int r = lane & 15, m4 = 4 * (lane >> 4);
     // the thread's input angles before the weights: loads return in order
@@ -224,7 +237,7 @@ __global__ __launch_bounds__(512) void k_mlp_forward(const uint16_t* __restrict_
         o.x[(size_t)(row0 + m) * INP + ec] = e;
     }
     __syncthreads();
-    transpose32(act[0], o.xt, P, row0);
+    if constexpr (SAVE_T) transpose32<MT>(act[0], o.xt, P, row0);
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
         const uint16_t* A = act[l & 1];
@@ -246,7 +259,7 @@ __global__ __launch_bounds__(512) void k_mlp_forward(const uint16_t* __restrict_
                     v[e] = f2bf((z > 0.0f || z != z) ? z : 0.0f);
                     O[(m + e) * ACT_LD + n] = v[e];
                 }
-                *reinterpret_cast<uint2*>(o.ht[l] + (size_t)n * P + row0 + m) = pack4(v);
+                if constexpr (SAVE_T) *reinterpret_cast<uint2*>(o.ht[l] + (size_t)n * P + row0 + m) = pack4(v);
             }
         }
         __syncthreads();
@@ -288,6 +301,7 @@ struct BwdChain {
 
 __global__ __launch_bounds__(512) void k_bwd_chain(BwdChain c, int P)
 {
+    constexpr int MT = TRAIN_MT, RB = 16 * MT;
     __shared__ __attribute__((aligned(16))) uint16_t up[2][RB * ACT_LD];
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -313,7 +327,7 @@ __global__ __launch_bounds__(512) void k_bwd_chain(BwdChain c, int P)
                     *reinterpret_cast<const uint2*>(c.ht[l] + (size_t)(n0 + 16 * j + r) * P + row0 + 16 * i + m4);
     if (t < 4 * RB) *reinterpret_cast<uint4*>(up[0] + (t >> 2) * ACT_LD + (t & 3) * 8) = dy;
     __syncthreads();
-    transpose32(up[0], c.dyt, P, row0);
+    transpose32<MT>(up[0], c.dyt, P, row0);
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
         const int l = 2 - s;   // the gradient of h_{l + 1}
@@ -817,8 +831,15 @@ int sdf_mlp_forward(const uint16_t* w16, const float* master, const float* q, in
     }
     o.y32 = reinterpret_cast<float*>(w + L.y);
     o.y = y;
-    hipLaunchKernelGGL(k_mlp_forward, dim3((P / RB + 7) / 8 * 8), dim3(512), 0, as_stream(stream), w16, master, q, (int)n_rows,
-                       idx, (int)batch, P, o);
+    auto go = [&](auto kernel, int rows) {
+        hipLaunchKernelGGL(kernel, dim3((P / rows + 7) / 8 * 8), dim3(512), 0, as_stream(stream), w16, master, q,
+                           (int)n_rows, idx, (int)batch, P, o);
+    };
+    // more rows than a backward pass takes: 64 per work-group, or the weights are
+    // read from the L2 for every 16, and without the transposed copies (12,288 rows 34
+    // us, 65,536 164; 19 and 67 like this)
+    if (P > TRAIN_ROWS) go(k_mlp_forward<4>, 16 * 4);
+    else go(k_mlp_forward<TRAIN_MT>, 16 * TRAIN_MT);
     return check_launch("k_mlp_forward");
 }
 
@@ -844,7 +865,8 @@ int sdf_mlp_backward(const uint16_t* w16, const float* target, int32_t n_rows, c
     const int KS = dw_chunks(P);
     const hipStream_t st = as_stream(stream);
     const int nblk = (P * OUTP + 255) / 256;
-    if (nblk > 1024) {
+    static_assert(TRAIN_ROWS * OUTP / 256 == 1024, "one loss partial sum per work-group");
+    if (P > TRAIN_ROWS) {
         set_error("sdf_mlp_backward: batch too large for the loss reduction");
         return EDT_ERR_UNSUPPORTED;
     }
@@ -855,7 +877,7 @@ int sdf_mlp_backward(const uint16_t* w16, const float* target, int32_t n_rows, c
     if (rc) return rc;
     const BwdChain c{u16(L.dy), u16(L.w4t), u16(L.w3t), u16(L.w2t), {u16(L.h1t), u16(L.h2t), u16(L.h3t)},
                      u16(L.dyt), {u16(L.d1t), u16(L.d2t), u16(L.d3t)}};
-    hipLaunchKernelGGL(k_bwd_chain, dim3((P / RB + 7) / 8 * 8), dim3(512), 0, st, c, P);
+    hipLaunchKernelGGL(k_bwd_chain, dim3((P / (16 * TRAIN_MT) + 7) / 8 * 8), dim3(512), 0, st, c, P);
     if ((rc = check_launch("k_bwd_chain"))) return rc;
     const DwArgs d{{u16(L.d1t), u16(L.d2t), u16(L.d3t), u16(L.dyt)},
                    {u16(L.xt), u16(L.h1t), u16(L.h2t), u16(L.h3t)}, gpart};
