@@ -66,11 +66,10 @@ constexpr int W = 16;           // positions on either side of a block that the 
 // ---------------------------------------------------------------------------
 // occupancy bits (the input of step 1): bit mis + lin = voxel lin is occupied,
 // mis = the occupancy pointer's offset from a 16-byte boundary.  They live in
-// the d2 buffer, which the xy pass does not use and the z pass overwrites.
+// the d2 buffer, which the xy pass does not use and the z pass overwrites, and fit
+// with the words that a row's last reads touch: a map that takes bits has more than
+// 64 voxels, and (n + 15) / 32 + 2 ntx + 1 words are fewer than n.
 // ---------------------------------------------------------------------------
-// Words written plus the ones a row's last reads may touch, in a d2 of n words.
-__host__ __device__ inline bool bits_fit(int64_t n) { return n >= 16; }
-
 __host__ __device__ inline int misalignment(const void* occ) { return (int)((uintptr_t)occ & 15u); }
 
 // 0x80 in every byte of w that is not zero
@@ -453,8 +452,9 @@ __device__ __forceinline__ void z_band(const ZTile& t, int np, uint32_t* lds)
 
 // ---------------------------------------------------------------------------
 // xy pass (steps 2-3): tile T = z * ntx + x0 / 64, one wave per band of BAND
-// rows, from the map's occupancy bits.  Writes the 2D site x' | y' << 16 of
-// every voxel of the tile (0xFFFFFFFF if the slice is empty).
+// rows, from the map's occupancy bits, or with occ given (ntx = 1, n voxels) from
+// its bytes.  Writes the 2D site x' | y' << 16 of every voxel of the tile
+// (0xFFFFFFFF if the slice is empty).
 //   lds   np * 128 bytes of x - x' [row][lane], then np / C * 128 bytes of
 //         chunk minima of |x - x'|, np = BAND * waves >= ny
 // ---------------------------------------------------------------------------
@@ -472,9 +472,44 @@ __device__ __forceinline__ uint32_t ffbl(uint32_t v)
     return r;
 }
 
+// The occupancy bits of a wave's band, voxels f0 .. f1 - 1 (at most 64 BAND), into
+// local memory (at most 2 BAND + 2 words): bit mis + i = voxel f0 + i, mis returned.
+template <int BAND>
+__device__ __forceinline__ int band_bits(const uint8_t* __restrict__ occ, int64_t n, int64_t f0, int64_t f1,
+                                         uint32_t* words)
+{
+    const int mis = misalignment(occ + f0);
+    const int lane = threadIdx.x & 63;
+    constexpr int U = (64 * BAND + 15 + 1023) / 1024;   // 64 chunks of 16 voxels each
+    uint32_t m[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const int64_t f = f0 - mis + 1024 * j + 16 * lane;
+        m[j] = 0;
+        if (f < f1) {
+            if (f >= 0 && f + 16 <= n) {
+                m[j] = chunk_bits(*reinterpret_cast<const uint4*>(occ + f));
+            } else {
+                for (int k = 0; k < 16; ++k)
+                    if (f + k >= 0 && f + k < n && occ[f + k]) m[j] |= 1u << k;
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const uint32_t o = __builtin_amdgcn_update_dpp(0, m[j], 0xF5, 0xF, 0xF, true);   // as in map_bits
+        const int c = 64 * j + lane;
+        if ((lane & 1) == 0 && c / 2 < 2 * BAND + 2) words[c / 2] = m[j] | o << 16;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return mis;
+}
+
 template <int NMAX, int C, int BAND>
-__device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int mis, uint32_t* __restrict__ out,
-                                        int nx, int ny, int ntx, int T, int np, uint32_t* lds)
+__device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int mis, const uint8_t* __restrict__ occ,
+                                        int64_t n, uint32_t* __restrict__ out, int nx, int ny, int ntx, int T, int np,
+                                        uint32_t* lds)
 {
     int16_t* dx = reinterpret_cast<int16_t*>(lds);
     uint16_t* cm = reinterpret_cast<uint16_t*>(dx + np * 64);
@@ -499,7 +534,22 @@ __device__ __forceinline__ void xy_tile(const uint32_t* __restrict__ bits, int m
         constexpr int NW = AXIS_MAX / 64;
         uint32_t wl = 0, wh = 0;
         int l = LEFT_NONE, r = RIGHT_NONE;
-        if (lane < BAND && q0 + lane < q1) {
+        if (occ) {
+            // in the place of the band's first rows, which come after
+            uint32_t* words = lds + q0 * 32;
+            const int64_t f0 = ((int64_t)z * ny + q0) * nx;
+            const int off = band_bits<BAND>(occ, n, f0, f0 + max(q1 - q0, 0) * nx, words);
+            if (lane < BAND && q0 + lane < q1) {
+                const unsigned b = off + lane * nx;
+                const uint32_t *p = words + (b >> 5), d0 = p[0], d1 = p[1], d2 = p[2];
+                wl = __builtin_amdgcn_alignbit(d1, d0, b);
+                wh = __builtin_amdgcn_alignbit(d2, d1, b);
+                wl &= nx < 32 ? (1u << nx) - 1u : ~0u;
+                wh &= nx < 64 ? (nx > 32 ? (1u << (nx - 32)) - 1u : 0u) : ~0u;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        } else if (lane < BAND && q0 + lane < q1) {
             const unsigned b = ((unsigned)z * ny + q0 + lane) * nx + mis;
             const uint32_t* p = bits + (b >> 5);
             uint32_t d[2 * NW + 1];
