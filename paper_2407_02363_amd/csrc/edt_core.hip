@@ -352,7 +352,7 @@ int launch_xy_tw(const EdtMapSet& s, hipStream_t st)
 template <int TW, bool WIDE, int NTZ>
 int launch_z_t(const EdtMapSet& s, hipStream_t st)
 {
-    if (TW == 64 && NTZ == 256 && !WIDE) {
+    if constexpr (TW == 64 && NTZ == 256 && !WIDE) {
         // search tiles: 64 consecutive columns of the xy plane each
         static thread_local EdtMapSet r;
         r = s;
@@ -362,13 +362,14 @@ int launch_z_t(const EdtMapSet& s, hipStream_t st)
             r.total += (s.m[i].nx * s.m[i].ny + 63) / 64;
         }
         return launch_search(r, true, st);
+    } else {
+        static bool done = false;
+        int rc = allow_lds(k_edt_z<TW, WIDE, NTZ>, done);
+        if (rc) return rc;
+        hipLaunchKernelGGL((k_edt_z<TW, WIDE, NTZ>), dim3(s.total), dim3(NTZ), z_lds(TW, s.nz_max, NTZ), st,
+                           s);
+        return check_launch("k_edt_z");
     }
-    static bool done = false;
-    int rc = allow_lds(k_edt_z<TW, WIDE, NTZ>, done);
-    if (rc) return rc;
-    hipLaunchKernelGGL((k_edt_z<TW, WIDE, NTZ>), dim3(s.total), dim3(NTZ), z_lds(TW, s.nz_max, NTZ), st,
-                       s);
-    return check_launch("k_edt_z");
 }
 
 template <int TW, int NTZ>
