@@ -3,6 +3,7 @@
 // launchers and the tile heuristics.  The tile code is in edt_search.h (maps
 // with every axis up to 512) and edt_tiles.h (every shape and tiling).
 #include <algorithm>
+#include <atomic>
 
 #include "edt_search.h"
 
@@ -169,18 +170,23 @@ __global__ __launch_bounds__(64 * NMAX / BAND) void k_edt_xy_search(Set s, int w
 }
 
 // Allow dynamic LDS beyond the 64 KiB default (gfx950 has 160 KiB per
-// work-group); once per kernel instantiation.
+// work-group); once per kernel instantiation and device, whose bit in done says so.
+using DeviceBits = std::atomic<uint64_t>;
 template <typename K>
-int allow_lds(K kernel, bool& done)
+int allow_lds(K kernel, DeviceBits& done)
 {
-    if (done) return EDT_OK;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 8192);
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+    if (e == hipSuccess && (done.load(std::memory_order_relaxed) & bit)) return EDT_OK;
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                160 * 1024 - 8192);
     if (e != hipSuccess) {
         set_error("hipFuncSetAttribute: %s", hipGetErrorString(e));
         return EDT_ERR_HIP;
     }
-    done = true;
+    done.fetch_or(bit, std::memory_order_relaxed);
     return EDT_OK;
 }
 
@@ -267,13 +273,13 @@ int launch_search_t(const EdtMapSet& s, bool z_pass, int n, hipStream_t st)
     // (512 x 512 x 128 frame 84 against 93 us, 512^3 blobs 431 against 436)
     constexpr int C = NMAX <= 256 ? 4 : 8;
     const int nw = (n + BAND - 1) / BAND, np = nw * BAND;
-    auto go = [&](auto kernel, bool& done, size_t lds, const auto& arg, const char* name, int grid) -> int {
+    auto go = [&](auto kernel, DeviceBits& done, size_t lds, const auto& arg, const char* name, int grid) -> int {
         int rc = allow_lds(kernel, done);
         if (rc) return rc;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * nw), lds, st, arg, nw, s.total);
         return check_launch(name);
     };
-    static bool done[4];
+    static DeviceBits done[4];
     if (z_pass) {
         const size_t lds = (size_t)(np + np / C) * 256;
         if constexpr (NMAX > 256) {
@@ -328,14 +334,14 @@ int launch_xy_w(const EdtMapSet& s, hipStream_t st)
     if (rows_first(s)) {
         int rc = launch_row_records(s, st);
         if (rc) return rc;
-        static bool done_rows = false;
+        static DeviceBits done_rows;
         rc = allow_lds(k_edt_xy_rows<TW, WIDE, NTX>, done_rows);
         if (rc) return rc;
         hipLaunchKernelGGL((k_edt_xy_rows<TW, WIDE, NTX>), dim3(s.total), dim3(NTX),
                            xy_rows_lds(TW, s.ny_max, NTX), st, s);
         return check_launch("k_edt_xy_rows");
     }
-    static bool done = false;
+    static DeviceBits done;
     int rc = allow_lds(k_edt_xy<TW, WIDE, NTX>, done);
     if (rc) return rc;
     hipLaunchKernelGGL((k_edt_xy<TW, WIDE, NTX>), dim3(s.total), dim3(NTX), xy_lds(TW, s.ny_max, NTX),
@@ -363,7 +369,7 @@ int launch_z_t(const EdtMapSet& s, hipStream_t st)
         }
         return launch_search(r, true, st);
     } else {
-        static bool done = false;
+        static DeviceBits done;
         int rc = allow_lds(k_edt_z<TW, WIDE, NTZ>, done);
         if (rc) return rc;
         hipLaunchKernelGGL((k_edt_z<TW, WIDE, NTZ>), dim3(s.total), dim3(NTZ), z_lds(TW, s.nz_max, NTZ), st,

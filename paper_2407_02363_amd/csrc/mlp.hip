@@ -932,14 +932,10 @@ int sdf_mlp_infer(const uint16_t* w16, const float* master, const float* q, int3
     }
     // one work-group per CU at most; tiles of 16 rows while that gives every
     // one at most two, else 64
-    static int n_cu = 0;
-    if (!n_cu) {
-        int dev = 0, c = 0;
-        n_cu = hipGetDevice(&dev) == hipSuccess &&
-                       hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && c > 0
-                   ? c
-                   : 256;
-    }
+    int dev = 0, n_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
+        n_cu = 256;
     const bool small = batch <= 2 * 16 * n_cu;
     const int rows = small ? 16 : 64;
     const dim3 grid(std::min((batch + rows - 1) / rows, n_cu));
