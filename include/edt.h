@@ -471,6 +471,8 @@ int edt_autotune_batched(const edt_batch_map_t* maps, int32_t n_maps, void* ws, 
  *                          entry (tiles the library cannot launch for that
  *                          shape), fails with EDT_ERR_ARG and adds nothing.
  *   edt_tuning_cache_clear forgets every entry (the heuristic tiles apply).
+ * An entry says which tiles were the fastest when it was made, not with which
+ * kernels: after an update of the library, tune again.
  * File format: the line "edtmi tuning cache v1", then one entry per line,
  *   single <arch> <nx> <ny> <nz> xy <xy_tile> <xy_group> z <z_tile> <z_group>
  *   batch <arch> <maps> <nx> <ny> <nz> xy <xy_tile> <xy_group> z <z_tile> <z_group>

@@ -23,8 +23,9 @@
  * it in step) that the matrix kernels read.  Gradients use the same layout.
  *
  * Conventions as in edt.h: device pointers, caller-owned buffers, stream as
- * void*, nothing allocated, negative status on error.  Any batch >= 1 works:
- * the workspace pads it to a multiple of 64 rows internally.
+ * void*, nothing allocated, negative status on error.  Any batch >= 1 works
+ * (for the backward pass up to 8192): the workspace pads it to a multiple of 64
+ * rows internally.
  */
 #ifndef EDTMI_SDF_MLP_H
 #define EDTMI_SDF_MLP_H
@@ -55,8 +56,10 @@ enum {
     SDF_MLP_PARAMS = 148256
 };
 
-/* Workspace bytes for a batch (encoded inputs, saved activations, outputs,
- * gradients of the backward pass, loss and weight-gradient partial sums). */
+/* Workspace bytes for a batch (encoded inputs, saved activations, outputs, and
+ * up to 8192 rows, the most that sdf_mlp_backward takes, the gradients of the
+ * backward pass, loss and weight-gradient partial sums).  A workspace serves any
+ * smaller batch too. */
 size_t sdf_mlp_workspace_bytes(int32_t batch);
 
 /* w16 = bfloat16(master), element by element (round to nearest even). */
@@ -93,7 +96,8 @@ int sdf_mlp_forward(const uint16_t* w16, const float* master, const float* q, in
  * dY and every masked upstream gradient are rounded to bfloat16 before
  * they enter a matrix product.  Weight and bias gradients reduce over the
  * batch in fixed-size chunks whose partial sums are added in chunk order
- * (no atomics), so two runs give identical bits.
+ * (no atomics), so two runs give identical bits.  More than 8192 rows fail
+ * with EDT_ERR_UNSUPPORTED.
  */
 int sdf_mlp_backward(const uint16_t* w16, const float* target, int32_t n_rows, const int32_t* idx,
                      int32_t batch, float clip_vox, float* grad, float* loss, void* ws,
@@ -124,8 +128,9 @@ int sdf_mlp_fallback(const float* y, const float* radii, const float* eps_vox, i
 
 /*
  * sdf_mlp_infer -- sdf_mlp_forward for inference: the same predictions, bit
- * for bit, in one launch (one work-group per 64 states, the activations kept
- * on chip), with no workspace and nothing kept for a backward pass.
+ * for bit, in one launch (at most one work-group per CU, each over tiles of 16
+ * or 64 states, the activations kept on chip), with no workspace and nothing
+ * kept for a backward pass.
  *   q     float32 [batch][7] joint angles, radians, device.
  *   y     float32 [batch][12] out, voxels, device.
  *   need  int32 [batch] out (nullable): when given, the fallback rule of

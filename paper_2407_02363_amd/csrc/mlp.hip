@@ -2,16 +2,17 @@
 // the backward pass and Adam, plus the exact-EDT fallback rule.
 //
 // A training step is six launches; at these sizes (4096 rows, 0.15 M weights,
-// 3.6 GFLOP) it is bound by launches and by each one's loads (290 KB of
-// weights per work-group take 5.7 of k_mlp_forward's 12 us), not by the matrix
-// cores:
-//   k_mlp_forward  the whole forward pass, a work-group per 16 rows   15.0 us
-//   k_bwd_pre      loss partials and dY; W2, W3, W4 transposed         3.8
-//   k_bwd_chain    the upstream gradients, 16 rows per work-group     13.5
-//   k_dw           weight and bias gradients' partial sums            15.1
-//   k_reduce_grad  the partial sums in chunk order, and the loss       4.0
-//   k_adam                                                             3.2
-// (batch 4096; 52 us a step, 143 with a launch per layer and product).
+// 3.6 GFLOP) it is bound by launches and by each one's loads (of k_mlp_forward,
+// reading 290 KB of weights per work-group takes 5.7 us, the products 4.4), not by
+// the matrix cores:
+//   k_mlp_forward  the whole forward pass, a work-group per 16 rows   14.7 us
+//   k_bwd_pre      loss partials and dY; W2, W3, W4 transposed         3.9
+//   k_bwd_chain    the upstream gradients, 16 rows per work-group     13.4
+//   k_dw           weight and bias gradients' partial sums            15.0
+//   k_reduce_grad  the partial sums in chunk order, and the loss       4.2
+//   k_adam                                                             3.1
+// (batch 4096, each kernel alone in the profiler; a step in a stream takes 48 us,
+// 143 with a launch per layer and product).
 // All products are v_mfma_f32_16x16x32_bf16 over K in ascending steps of 32.
 // Lane l of an MFMA holds A[l % 16][8 (l / 16) + i], B[8 (l / 16) + i][l % 16]
 // and C[4 (l / 16) + i][l % 16], so an operand whose reduction index is
