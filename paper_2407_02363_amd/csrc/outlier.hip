@@ -159,10 +159,13 @@ __global__ __launch_bounds__(SAMPLES) void k_sor_zero(uint4* __restrict__ count,
 }
 static_assert(2 * SLOTS == 4 * SAMPLES, "one 16-byte store per thread clears the table");
 
-// Cell size: h1, or half of it for search_dense.
-__device__ __forceinline__ float cell_size(float h1, const unsigned long long* acc)
+// Cell sizes of the two searches.
+struct Cells {
+    float r, half_r;   // 1.001 R and half of it
+};
+__device__ __forceinline__ float cell_size(const Cells& c, const unsigned long long* acc)
 {
-    return acc[ACC_DENSE] ? 0.5f * h1 : h1;
+    return acc[ACC_DENSE] ? c.half_r : c.r;
 }
 
 // Neighbouring points of a frame tend to share a bucket, and atomics on one
@@ -197,7 +200,7 @@ __device__ __forceinline__ Run same_bucket_run(unsigned b)
 
 // Counts the finite points per bucket; a point that is not finite gets its
 // mean distance (NaN) here, since the neighbour search never sees it.
-__global__ void k_sor_count(const float* __restrict__ pts, int64_t n, float h1, Wrap w,
+__global__ void k_sor_count(const float* __restrict__ pts, int64_t n, Cells cells, Wrap w,
                             unsigned* __restrict__ count, float* __restrict__ dmean,
                             const unsigned long long* __restrict__ acc)
 {
@@ -208,7 +211,7 @@ __global__ void k_sor_count(const float* __restrict__ pts, int64_t n, float h1, 
         dmean[i] = __builtin_nanf("");
         return;
     }
-    const float h = cell_size(h1, acc);
+    const float h = cell_size(cells, acc);
     const unsigned b = bucket(cell_of(x, h), cell_of(y, h), cell_of(z, h), w);
     const Run r = same_bucket_run(b);
     if (r.first) atomicAdd(count + b, (unsigned)r.n);
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(256) void k_sor_place(const uint4* __restrict__ cou
 }
 
 // Takes the places of a bucket from its last one down: count is used up.
-__global__ void k_sor_scatter(const float* __restrict__ pts, int64_t n, float h1, Wrap w,
+__global__ void k_sor_scatter(const float* __restrict__ pts, int64_t n, Cells cells, Wrap w,
                               const uint2* __restrict__ table, unsigned* __restrict__ count,
                               float4* __restrict__ spts, const unsigned long long* __restrict__ acc)
 {
@@ -265,7 +268,7 @@ __global__ void k_sor_scatter(const float* __restrict__ pts, int64_t n, float h1
     if (i >= n) return;
     const float x = pts[3 * i], y = pts[3 * i + 1], z = pts[3 * i + 2];
     if (!finite3(x, y, z)) return;
-    const float h = cell_size(h1, acc);
+    const float h = cell_size(cells, acc);
     const unsigned b = bucket(cell_of(x, h), cell_of(y, h), cell_of(z, h), w);
     const Run r = same_bucket_run(b);
     unsigned left = 0;   // points of the bucket still to place before the run's
@@ -467,7 +470,7 @@ constexpr int COPY_ROWS = 4;
 static_assert(3 * CAP >= 36 * 64, "18 ranges per lane");
 
 template <int K>
-__global__ __launch_bounds__(64) void k_sor_knn(int k, float R, float h, Wrap w,
+__global__ __launch_bounds__(64) void k_sor_knn(int k, float R, Cells cells, Wrap w,
                                                 const uint2* __restrict__ table,
                                                 const float4* __restrict__ spts,
                                                 float* __restrict__ dmean,
@@ -486,12 +489,13 @@ __global__ __launch_bounds__(64) void k_sor_knn(int k, float R, float h, Wrap w,
     const int i = __float_as_int(P.w);
     if (acc[ACC_DENSE]) {
         if (active) {
-            d = search_dense<K>(P, k, R, 0.5f * h, w, table, spts);
+            d = search_dense<K>(P, k, R, cells.half_r, w, table, spts);
             dmean[i] = d;
         }
         add_statistics(active, d, acc);
         return;
     }
+    const float h = cells.r;
     const float px = P.x, py = P.y, pz = P.z;
     const float rr = R * R;
     const int cx = cell_of(px, h), cy = cell_of(py, h), cz = cell_of(pz, h);
@@ -744,7 +748,7 @@ int edt_outlier_filter(const float* pts, int64_t n, int32_t k, float radius, flo
     unsigned long long* acc = reinterpret_cast<unsigned long long*>(w + L.acc);
     float* dm = mean_dist ? mean_dist : reinterpret_cast<float*>(w + L.total);
     const int T = (int)L.tmask + 1;
-    const float h = radius * 1.001f;
+    const Cells cells{radius * 1.001f, radius * 0.5005f};
     const hipStream_t st = as_stream(stream);
     const unsigned pblocks = (unsigned)((std::max<int64_t>(n, 1) + 255) / 256);
     const int est = n > FEW ? 1 : 0;
@@ -753,19 +757,21 @@ int edt_outlier_filter(const float* pts, int64_t n, int32_t k, float radius, flo
     int rc = check_launch("k_sor_zero");
     if (rc) return rc;
     if (n > 0) {
-        hipLaunchKernelGGL(k_sor_count, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, count, dm, acc);
+        hipLaunchKernelGGL(k_sor_count, dim3(pblocks), dim3(256), 0, st, pts, n, cells, L.wrap, count, dm, acc);
         if ((rc = check_launch("k_sor_count"))) return rc;
         hipLaunchKernelGGL(k_sor_place, dim3((T / 4 + 256 * PLACE_PER - 1) / (256 * PLACE_PER)), dim3(256), 0, st,
                            reinterpret_cast<const uint4*>(count), T / 4, reinterpret_cast<uint4*>(table), acc);
         if ((rc = check_launch("k_sor_place"))) return rc;
-        hipLaunchKernelGGL(k_sor_scatter, dim3(pblocks), dim3(256), 0, st, pts, n, h, L.wrap, table, count, spts,
+        hipLaunchKernelGGL(k_sor_scatter, dim3(pblocks), dim3(256), 0, st, pts, n, cells, L.wrap, table, count, spts,
                            acc);
         if ((rc = check_launch("k_sor_scatter"))) return rc;
         const dim3 waves((unsigned)((n + 63) / 64));
         if (k <= 8)
-            hipLaunchKernelGGL(k_sor_knn<8>, waves, dim3(64), 0, st, (int)k, radius, h, L.wrap, table, spts, dm, acc);
+            hipLaunchKernelGGL(k_sor_knn<8>, waves, dim3(64), 0, st, (int)k, radius, cells, L.wrap, table, spts, dm,
+                               acc);
         else
-            hipLaunchKernelGGL(k_sor_knn<KMAX>, waves, dim3(64), 0, st, (int)k, radius, h, L.wrap, table, spts, dm, acc);
+            hipLaunchKernelGGL(k_sor_knn<KMAX>, waves, dim3(64), 0, st, (int)k, radius, cells, L.wrap, table, spts, dm,
+                               acc);
         if ((rc = check_launch("k_sor_knn"))) return rc;
     }
     hipLaunchKernelGGL(k_sor_keep, dim3(pblocks), dim3(256), 0, st, pts, n, dm, acc, (double)alpha,
